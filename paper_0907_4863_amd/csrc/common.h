@@ -19,7 +19,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <initializer_list>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "../../include/saamg.h"
@@ -202,10 +204,12 @@ enum TimerKind {
 };
 struct KTimer {
     int slot = -1;
-    int kind;
     hipStream_t s;
     bool started = false, stopped = false;
     KTimer(int kind, hipStream_t s, long units);
+    // one launch that does the work of several classes: each counts it, with its units and
+    // the share of its time that they have of all units given
+    KTimer(hipStream_t s, std::initializer_list<std::pair<int, long>> classes);
     hipEvent_t start();  // the start event for the first launch (null when off or taken)
     hipEvent_t stop();   // the stop event (null when off)
     ~KTimer();           // records the events that no launch carried
@@ -225,6 +229,13 @@ struct ChebCoef {
 };
 ChebCoef cheb_coefficients(double lam_hi, double ratio, int degree);
 
+// Blocks of a V-cycle stroke (stroke.hip): wavefronts per block, planes per slab, the tiles of
+// the cross-section that hold unknowns (and where their list starts in FineLevel::tiles), slabs.
+struct StrokeTile {
+    int W = 0, S = 0, live = 0, list = 0, gz = 0;
+    long blocks() const { return (long)live * gz; }
+};
+
 struct FineLevel {
     int nx, ny, nz, nsegx;
     int zb = 4;                 // planes per block of the solve-time kernels
@@ -239,6 +250,9 @@ struct FineLevel {
     uint64_t* irr = nullptr;
     int32_t* base = nullptr;    // table slot of each segment's first irregular row
     int32_t* base_full = nullptr;  // the same before de-duplication (one row per node)
+    uint8_t* zinfo = nullptr;   // [ny][nz + 1]: which planes share a line's rows (stroke.hip)
+    StrokeTile stroke[2][2];    // [fp32, fp64][down, up]
+    int32_t* tiles = nullptr;   // their lists of tiles
     long n_irr = 0;             // irregular rows
     long n_tab = 0;             // table rows: lines repeating the line one plane below share
                                 // its rows (see l0_dedup_table)

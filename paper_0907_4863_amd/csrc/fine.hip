@@ -854,6 +854,7 @@ void l0_dedup_table(FineLevel& L, const double* full64, const float* full32, hip
                        (const int32_t*)keep.as<int32_t>(), (const int32_t*)off.as<int32_t>(),
                        L.n_irr, (long)n_tab, full64, full32, L.tab64, L.tab32);
     HIPCHECK(hipGetLastError());
+    l0_zinfo(L, s);
     HIPCHECK(hipStreamSynchronize(s));
 }
 

@@ -144,6 +144,23 @@ template <typename T>
 void l0_prolong(const FineLevel& L, const CoarseLevel& C, const T* v, T* x, double omega,
                 hipStream_t s);
 
+// ---- level 0, whole strokes of the V-cycle (stroke.hip)
+// L.zinfo from L's masks and table (allocated on first use)
+void l0_zinfo(FineLevel& L, hipStream_t s);
+long zinfo_bytes(const FineLevel& L);
+// whether the level-0 V-cycle runs as strokes in a precision of `bytes` bytes
+bool l0_strokes(const FineLevel& L, int degree, int bytes);
+// down: x = degree-2 smoothing of f from zero, fc = P^T (f - A x), fd (nullable) = D^-1 fc of
+// level 1.  up: out = two smoothing steps on x + P v, partials of f . out (nullable) over
+// l0_stroke_parts blocks
+template <typename T>
+void l0_down(const FineLevel& L, const CoarseLevel& C, bool sym, const T* f, T* x, T* fc, T* fd,
+             double c1, double c2, double c20, double omega, hipStream_t s);
+template <typename T>
+void l0_up(const FineLevel& L, const CoarseLevel& C, const T* vc, const T* x, const T* f, T* out,
+           double c1, double c2, double c20, double omega, double* dot, hipStream_t s);
+long l0_stroke_parts(const FineLevel& L, int bytes);
+
 // ---- level 0 on 16-byte lanes (wide.hip; FineLevel::wide).  The launchers of fine.hip
 // dispatch to these; they take the caller's kernel timer.
 template <typename T>

@@ -239,8 +239,11 @@ struct VBuf {
     static long yz_size(const saamg_hierarchy* H) {
         return H->l0.nxy * ((H->l0.nz + 2) / 3);
     }
-    void alloc(const saamg_hierarchy* H) {
+    bool lean = false;             // level 0 runs as strokes, which keep x only
+    // strokes: leave out the level-0 vectors that only the step-by-step kernels use
+    void alloc(const saamg_hierarchy* H, bool strokes) {
         const int L = H->n_levels;
+        lean = strokes;
         f.assign(L, nullptr);
         xa.assign(L, nullptr);
         xb.assign(L, nullptr);
@@ -248,13 +251,13 @@ struct VBuf {
         for (int l = 0; l < L; ++l) {
             const long n = (l == 0) ? H->l0.nbox : H->lc[l - 1].nstore;
             xa[l] = (T*)dmalloc(sizeof(T) * n);
-            if (l < L - 1) {
+            if (l < L - 1 && !(lean && l == 0)) {
                 xb[l] = (T*)dmalloc(sizeof(T) * n);
                 d[l] = (T*)dmalloc(sizeof(T) * n);
             }
             if (l > 0) f[l] = (T*)dmalloc(sizeof(T) * n);
         }
-        if (L > 1) yz = (T*)dmalloc(sizeof(T) * yz_size(H));
+        if (L > 1 && !lean) yz = (T*)dmalloc(sizeof(T) * yz_size(H));
     }
     void release() {
         for (auto* v : {&f, &xa, &xb, &d})
@@ -270,10 +273,10 @@ struct VBuf {
         int64_t b = 0;
         for (int l = 0; l < H->n_levels; ++l) {
             const long n = (l == 0) ? H->l0.nbox : H->lc[l - 1].nstore;
-            int cnt = 1 + (l < H->n_levels - 1 ? 2 : 0) + (l > 0 ? 1 : 0);
+            int cnt = 1 + (l < H->n_levels - 1 && !(lean && l == 0) ? 2 : 0) + (l > 0 ? 1 : 0);
             b += (int64_t)cnt * n * sizeof(T);
         }
-        if (H->n_levels > 1) b += (int64_t)yz_size(H) * sizeof(T);
+        if (H->n_levels > 1 && !lean) b += (int64_t)yz_size(H) * sizeof(T);
         return b;
     }
 };
@@ -313,6 +316,14 @@ static T* vcycle(const saamg_hierarchy* H, VBuf<T>& B, int l, const T* f0, T* ou
     }
     const LevelParams& P = H->par[l];
     const ChebCoef& c = P.cheb;
+    if (fine && l0_strokes(H->l0, c.degree, (int)sizeof(T))) {
+        T* fd = H->n_levels > 2 ? B.xb[1] : nullptr;
+        l0_down<T>(H->l0, H->lc[0], H->sym, f0, B.xa[0], B.f[1], fd, c.c1[1], c.c2[1], c.c2[0],
+                   P.omega, s);
+        T* v = vcycle<T>(H, B, 1, nullptr, nullptr, nullptr, nullptr, s);
+        l0_up<T>(H->l0, H->lc[0], v, B.xa[0], f0, out, c.c1[1], c.c2[1], c.c2[0], P.omega, dot, s);
+        return out;
+    }
     const T* fl = fine ? nullptr : B.f[l];
     T* x = B.xa[l];
     T* other = B.xb[l];
@@ -433,10 +444,18 @@ static void ring_flush(saamg_state* S) {
 }
 
 // Partial sums written by the V-cycle's fused r . z (in the working precision).
-static long pc_parts(const saamg_state* S) { return l0_dot_parts(S->H->l0, S->mixed ? 4 : 8); }
+static bool strokes(const saamg_hierarchy* H, int bytes) {
+    return H->n_levels > 1 && l0_strokes(H->l0, H->par[0].cheb.degree, bytes);
+}
+static long pc_parts(const saamg_state* S) {
+    const int bytes = S->mixed ? 4 : 8;
+    return strokes(S->H, bytes) ? l0_stroke_parts(S->H->l0, bytes)
+                                : l0_dot_parts(S->H->l0, bytes);
+}
 
 // pinned = false: no pinned host buffer and no event (the allocation-free solve); the
-// scalars are read into the state itself and the host waits on the stream.
+// scalars are read into the state itself and the host waits on the stream, and every
+// V-cycle vector is taken, so that the sizes the static array serves stay what they were.
 static void state_alloc(saamg_state* S, saamg_hierarchy* H, bool pinned = true) {
     S->H = H;
     S->mixed = H->opt.precision == SAAMG_MIXED;
@@ -459,15 +478,16 @@ static void state_alloc(saamg_state* S, saamg_hierarchy* H, bool pinned = true) 
     // x, r, q, b~ (fp64); p, z and the fp32 copy of r
     S->bytes = 32L * n + (S->ringf ? (long)S->pw * S->ringk : 8) * n + 8L * n;  // z 8, or fp32 z and r32
     if (S->mixed) {
-        S->vf.alloc(H);
+        S->vf.alloc(H, pinned && strokes(H, 4));
         S->bytes += S->vf.bytes(H);
     } else {
-        S->vd.alloc(H);
+        S->vd.alloc(H, pinned && strokes(H, 8));
         S->bytes += S->vd.bytes(H);
     }
     S->npart = std::max<long>(l0_blocks(H->l0), 1);
     if (H->l0.wide)
         S->npart = std::max(S->npart, std::max(l0_wblocks(H->l0, 2), l0_wblocks(H->l0, 4)));
+    if (strokes(H, S->pw)) S->npart = std::max(S->npart, l0_stroke_parts(H->l0, S->pw));
     S->part = (double*)dmalloc(sizeof(double) * 3 * S->npart);
     S->scal = (double*)dmalloc(sizeof(double) * S_NSLOTS);
     if (!pinned) {
@@ -1090,7 +1110,7 @@ static saamg_hierarchy* setup_impl(const saamg_domain* dom, int variant, const s
         L.n_unknowns = tots[1];
         fine_numbers(L, dom, dd, variant, s);
         dd.release();
-        H->bytes = 24L * L.nseg + 8L * nbox + 12L * 16 * L.n_tab;
+        H->bytes = 24L * L.nseg + 8L * nbox + 12L * 16 * L.n_tab + zinfo_bytes(L);
         H->t_phase_ms[0] = t_host;
         H->t_phase_ms[1] = ms_since(t0) - t_host;
 
@@ -1212,9 +1232,9 @@ static void check_same_rows(const saamg_hierarchy* H, const DeviceDomain& dd, hi
 static void drop_operator(saamg_hierarchy* H) {
     if (!H->op) return;
     for (void* p : {(void*)H->op->tab64, (void*)H->op->tab32, (void*)H->op->sigma,
-                    (void*)H->op->base})
+                    (void*)H->op->base, (void*)H->op->zinfo})
         dfree(p);
-    H->bytes -= 8L * H->op->nbox + 4L * H->op->nseg + 12L * 16 * H->op->n_tab;
+    H->bytes -= 8L * H->op->nbox + 4L * H->op->nseg + 12L * 16 * H->op->n_tab + zinfo_bytes(H->l0);
     delete H->op;
     H->op = nullptr;
 }
@@ -1264,6 +1284,7 @@ static void set_operator_impl(saamg_hierarchy* H, const saamg_domain* dom, hipSt
         op->tab32 = nullptr;
         op->sigma = nullptr;
         op->base = nullptr;
+        op->zinfo = nullptr;
         try {
             op->base = (int32_t*)dmalloc(4 * L.nseg);
             op->sigma = (double*)dmalloc(8 * L.nbox);
@@ -1273,7 +1294,7 @@ static void set_operator_impl(saamg_hierarchy* H, const saamg_domain* dom, hipSt
             throw;
         }
         H->op = op;
-        H->bytes += 8L * L.nbox + 4L * L.nseg;
+        H->bytes += 8L * L.nbox + 4L * L.nseg + zinfo_bytes(L);
     }
     H->bytes -= 12L * 16 * H->op->n_tab;
     fine_numbers(*H->op, dom, dd, H->variant, s);
@@ -1495,7 +1516,7 @@ int saamg_destroy(saamg_hierarchy* H) {
     MemScope ms(H->mem, nullptr);
     FineLevel& L = H->l0;
     for (void* p : {(void*)L.unk, (void*)L.irr, (void*)L.base, (void*)L.base_full,
-                    (void*)L.tab64, (void*)L.tab32, (void*)L.sigma, (void*)H->Ainv,
+                    (void*)L.zinfo, (void*)L.tiles, (void*)L.tab64, (void*)L.tab32, (void*)L.sigma, (void*)H->Ainv,
                     (void*)H->cidx})
         dfree(p);
     for (auto& C : H->lc) free_coarse(C);

@@ -1,0 +1,927 @@
+// Level-0 strokes of the V-cycle: the degree-2 pre-smoothing, the residual and the
+// restriction in one pass over the lattice (down), and the prolongation with the degree-2
+// post-smoothing and the PCG's r . z in one pass (up).
+//
+// A block of W wavefronts marches along z over a tile of lines.  A wavefront owns 64
+// consecutive columns of 3 lines (one aggregate row), one column per lane and line, and
+// the block's first and last wavefronts are the halo lines: a pass applies three stencils
+// in a row, so the outputs lie 3 nodes inside the tile (2 for the up-stroke along x).
+// The stages run as a pipeline along z: at plane p the first stage forms plane p - 1, the
+// second p - 2, the third p - 3, each from the previous stage's three planes, which stay
+// in registers.  x-neighbours come from the adjacent lanes, y-neighbours inside the three
+// lines from registers; only the first and last line of each wavefront go through LDS,
+// double-buffered, so that a plane takes one barrier.
+//
+// A column's stencil row (the six neighbour coefficients; zeros where the node is not an
+// unknown) is held in registers and read again only where a line differs from the line one
+// plane below (FineLevel::zinfo), which a pipe of constant cross-section does at its ends
+// only: a plane then needs no masks, slots or table rows, and every lane runs the same
+// code whether its row is regular, irregular or empty.
+//
+// Why one pass: the seven step kernels moved 20 + 4 and 28 bytes a node in fp32 where the
+// strokes move 8 and 12, but each also paid a march's fixed cost per plane (masks, slots,
+// table rows, 5 to 9 loads a node), and on small boxes a launch of 4-5 us.  Vector
+// instructions bound the strokes (about 34 a node for the three stages of the down-stroke, 60%
+// of the issue slots busy on the largest boxes) and, on small boxes, the latency of a plane
+// step (0.45-0.6 us).  Time per V-cycle, step kernels -> down + up stroke:
+//   256 x 256 x 768 ellipse, quadratic rule, fp32   612 -> 128 + 176 us
+//   512^3 open tube, constant rule, fp32           1650 -> 320 + 463 us
+//   128 x 128 x 256 ellipse, quadratic rule, fp64   223 ->  32 +  33 us
+//   97 x 97 x 291 cavity with bore, fp32            118 ->  29 +  38 us
+//   33^3 cylinder, fp64                              34 ->  10 +  12 us
+#include "march.h"
+
+namespace saamg {
+
+template <typename T>
+struct StrokeView {
+    int nx, ny, nz, nsegx;
+    long nxy;
+    const uint64_t* unk;
+    const uint64_t* irr;
+    const int32_t* base;
+    const T* tab;
+    const T* tabT;
+    T c[3];
+    const uint8_t* zinfo;   // [ny][nz + 1], see k_zinfo
+    const int32_t* tiles;   // the tiles of the cross-section that hold unknowns: x + 65536 y
+    int live, S;            // their number; planes per slab (a multiple of 3)
+    const double* skip;
+};
+
+// Level 1 as the strokes address it.
+template <typename T>
+struct CoarseBox {
+    int mx, my, mz;
+    long sx, sxy;
+    const T* invD;
+};
+
+// Stencil rows of a wavefront's 3 x 64 columns on one plane.
+template <typename T, bool TR>
+struct Cols {
+    T a[3][6];
+    T at[TR ? 3 : 1][6];  // rows of the transpose
+    uint64_t um[3];       // the lanes whose node is an unknown
+};
+
+// What a line's entry of zinfo says (see k_zinfo).
+constexpr int kSlotRow = -1, kSlotNone = -2;
+constexpr int kZSame = 1, kZUnk = 2, kZRep = 2;  // bits, and the shift of 1 + (rep - z)
+
+// Whole-wavefront shift by one lane with 0 from beyond the wavefront (lane l receives lane
+// l - 1 (UP) or l + 1), in a form the compiler can fold into the consuming instruction.
+template <bool UP>
+__device__ __forceinline__ float shift0(float v) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v),
+                                                                 UP ? 0x138 : 0x130, 0xf, 0xf, true));
+}
+template <bool UP>
+__device__ __forceinline__ double shift0(double v) {
+    const uint64_t s = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)s, UP ? 0x138 : 0x130, 0xf, 0xf, true);
+    const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(s >> 32), UP ? 0x138 : 0x130, 0xf, 0xf, true);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+// One plane of a box vector as a bounds-checked buffer: a lane whose byte offset is kOff
+// reads 0 and writes nothing, and so does every lane on a plane that is not there (ok
+// false).  The march then needs no branch around its loads and stores.
+constexpr unsigned kOff = 0x80000000u;
+template <typename T>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t plane(const T* a, int bytes, bool ok) {
+    return __builtin_amdgcn_make_buffer_rsrc((void*)a, 0, ok ? bytes : 0, 0x00027000);
+}
+// The loaded values are first used here: keeps the compiler from moving the use (and the
+// wait for the load) ahead of the barrier before it.
+__device__ __forceinline__ float here(float v) {
+    asm volatile("" : "+v"(v));
+    return v;
+}
+__device__ __forceinline__ double here(double v) {
+    asm volatile("" : "+v"(v));
+    return v;
+}
+__device__ __forceinline__ void bload(__amdgpu_buffer_rsrc_t r, unsigned o, float& v) {
+    v = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)o, 0, 0));
+}
+__device__ __forceinline__ void bload(__amdgpu_buffer_rsrc_t r, unsigned o, double& v) {
+    v = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, (int)o, 0, 0));
+}
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ void bstore(__amdgpu_buffer_rsrc_t r, unsigned o, float v) {
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, (int)o, 0, 0);
+}
+__device__ __forceinline__ void bstore(__amdgpu_buffer_rsrc_t r, unsigned o, double v) {
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, (int)o, 0, 0);
+}
+
+// The rows in use along a slab.  Planes are counted from the slab's first, p0; up to 64.
+template <typename T, bool TR>
+struct Rows {
+    Cols<T, TR> c;
+    uint64_t change;  // planes whose rows differ from those of the plane below; bit 0 set
+    uint64_t unk;     // planes with an unknown in the wavefront's columns' lines
+    int info[3];      // zinfo of the lines at plane p0 + lane
+    // Groups are numbered from the slab's first plane; a wavefront keeps the table slots of its
+    // nodes (kSlotRow: the interior row, kSlotNone: not an unknown) for the last three groups
+    // it met in LDS, because the stages, on three consecutive planes, go back and forth between
+    // the groups where they change, and a row read again by its slot is one short trip to
+    // the cache instead of three.
+    int held = 0, newest = 0;
+    int* ring;  // [3 groups][3 lines][64]
+    // Planes i at which a pipeline of stages on planes i - first .. i - first - 2 runs with the
+    // rows it holds: all of them, and the one before, share one group's rows and have unknowns.
+    __device__ __forceinline__ uint64_t steady(int first) const {
+        const uint64_t go = unk & (unk << 1) & (unk << 2) & (unk << 3) &
+                            ~(change | (change << 1) | (change << 2));
+        return go << first;
+    }
+    __device__ __forceinline__ void init(const StrokeView<T>& v, int yb, int p0) {
+        const int z = p0 + (int)threadIdx.x;
+        int all = kZSame | kZUnk, any = 0;
+#pragma unroll
+        for (int l = 0; l < 3; ++l) {
+            const int y = yb + l;
+            info[l] = kZSame;
+            if ((unsigned)y < (unsigned)v.ny && z >= 0 && z <= v.nz)
+                info[l] = v.zinfo[(long)(v.nz + 1) * y + z];
+            all &= info[l];
+            any |= info[l];
+        }
+        change = ~__ballot(all & kZSame) | 1ull;
+        unk = __ballot(any & kZUnk);
+    }
+    // Rows of plane i into c; false (and c unchanged) where the lines hold no unknown.  FAST:
+    // on a steady plane they are there.
+    template <bool FAST>
+    __device__ __forceinline__ bool at(const StrokeView<T>& v, int x, int yb, int p0, int i) {
+        if (FAST) return true;
+        i = max(i, 0);
+        if (!((unk >> i) & 1ull)) return false;
+        const int g = (int)__popcll(change & ((2ull << i) - 1ull));
+        if (g != held) {
+            held = g;
+            load(v, x, yb, p0, i, g);
+        }
+        return true;
+    }
+    // Table slots of the lines on plane i.
+    struct Words {
+        uint64_t u[3], r[3];
+        int b0[3];
+    };
+    __device__ __forceinline__ Words words(const StrokeView<T>& v, int x, int yb, int p0, int i) {
+        Words q;
+#pragma unroll
+        for (int l = 0; l < 3; ++l) {
+            const int inf = __builtin_amdgcn_readlane(info[l], i);
+            const int y = yb + l, z = p0 + i + (inf >> kZRep) - 1;  // the plane that has the rows
+            q.u[l] = q.r[l] = 0;
+            q.b0[l] = 0;
+            if ((inf & kZUnk) && (unsigned)x < (unsigned)v.nx) {
+                const long s = ((long)z * v.ny + y) * v.nsegx + (x >> 6);
+                q.u[l] = v.unk[s];
+                q.r[l] = v.irr[s];
+                q.b0[l] = v.base[s];
+            }
+        }
+        return q;
+    }
+    // returns the lanes whose column holds an unknown
+    __device__ __forceinline__ uint64_t keep(const Words& q, int x, int g) {
+        int* e = ring + (g % 3) * 192 + threadIdx.x;
+        const int b = x & 63;
+        bool u = false;
+#pragma unroll
+        for (int l = 0; l < 3; ++l) {
+            const bool un = (q.u[l] >> b) & 1ull;
+            u = u || un;
+            e[64 * l] = !un ? kSlotNone
+                        : !((q.r[l] >> b) & 1ull) ? kSlotRow
+                                                  : q.b0[l] + (int)__popcll(q.r[l] & ((1ull << b) - 1ull));
+        }
+        return __ballot(u);
+    }
+    // The slots of the first three groups of the n planes the slab's stages visit, read
+    // together: their trips to memory overlap each other and the march's first planes.  False
+    // when the columns of `out` (the lanes whose nodes the wavefront writes) hold no unknown.
+    __device__ __forceinline__ bool preload(const StrokeView<T>& v, int x, int yb, int p0, int n,
+                                            uint64_t out) {
+        const uint64_t in = n < 64 ? (1ull << n) - 1ull : ~0ull;
+        Words q[3];
+        int gs[3];
+        uint64_t left = unk & in;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            gs[k] = 0;
+            if (left == 0) continue;  // wave-uniform
+            const int i = (int)__builtin_ctzll(left);
+            gs[k] = (int)__popcll(change & ((2ull << i) - 1ull));
+            q[k] = words(v, x, yb, p0, i);
+            // the planes beyond this group
+            const uint64_t later = change & ~((2ull << i) - 1ull);
+            left &= later ? ~((later & (0 - later)) - 1ull) : 0ull;
+        }
+        // the lines know their unknowns, not the columns: a wavefront whose columns hold none
+        // (beside the pipe, most often) has no plane to work on
+        bool all = left == 0;
+        uint64_t some = 0;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            if (gs[k] <= newest) continue;
+            if (gs[k] >= gs[0] + 3) {
+                all = false;
+                continue;
+            }
+            some |= keep(q[k], x, gs[k]);
+            newest = gs[k];
+        }
+        if (all && some == 0) unk = 0;
+        return out != 0 && unk != 0 && (!all || (some & out) != 0);
+    }
+    __device__ __forceinline__ void load(const StrokeView<T>& v, int x, int yb, int p0, int i, int g) {
+        if (g > newest) {  // the first stage meets the groups in order
+            newest = g;
+            (void)keep(words(v, x, yb, p0, i), x, g);
+        }
+        const int* e = ring + (g % 3) * 192 + threadIdx.x;
+        int slot[3];
+#pragma unroll
+        for (int l = 0; l < 3; ++l) slot[l] = e[64 * l];
+#pragma unroll
+        for (int l = 0; l < 3; ++l) {
+            c.um[l] = __ballot(slot[l] != kSlotNone);
+#pragma unroll
+            for (int d = 0; d < 6; ++d) {
+                c.a[l][d] = slot[l] != kSlotNone ? v.c[d >> 1] : T(0);
+                if (TR) c.at[l][d] = c.a[l][d];
+            }
+            if (slot[l] >= 0) {
+                load_row6(v.tab, (long)slot[l], 0u, c.a[l]);
+                if (TR) load_row6(v.tabT, (long)slot[l], 0u, c.at[l]);
+            }
+        }
+        // the rows have landed before the branch around this read ends, so that the common
+        // path waits for none of them (nor, with them, for the planes in flight)
+        settle(c.a);
+        if (TR) settle(c.at);
+    }
+};
+
+// (A X) on the three lines of a wavefront: own lines c, the planes below and above, the
+// lines before and after (ylo, yhi).
+template <typename T>
+__device__ __forceinline__ void apply3(const T (&a)[3][6], const T (&c)[3], const T (&zm)[3],
+                                       const T (&zp)[3], T ylo, T yhi, T (&o)[3]) {
+#pragma unroll
+    for (int l = 0; l < 3; ++l) {
+        const T ym = l ? c[l - 1] : ylo, yp = l < 2 ? c[l + 1] : yhi;
+        o[l] = c[l] + shift0<true>(c[l]) * a[l][0] + shift0<false>(c[l]) * a[l][1] + a[l][2] * ym +
+               a[l][3] * yp + a[l][4] * zm[l] + a[l][5] * zp[l];
+    }
+}
+
+// Barrier of a plane step: the LDS writes of the step are visible after it; loads and
+// stores of device memory stay in flight.
+__device__ __forceinline__ void step_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// Tile of a block (the live tiles along x, then y, then slabs; neighbours in this order share
+// an XCD's L2: each XCD takes a run of consecutive tiles).
+template <typename T>
+__device__ __forceinline__ void stroke_tile(const StrokeView<T>& v, int* tx, int* ty, int* sz) {
+    const unsigned b = blockIdx.x, nb = gridDim.x, q = nb >> 3;
+    const unsigned lb = (b < 8 * q) ? (b & 7) * q + (b >> 3) : b;
+    const int32_t t = v.tiles[lb % (unsigned)v.live];
+    *tx = t & 0xffff;
+    *ty = t >> 16;
+    *sz = (int)(lb / (unsigned)v.live);
+}
+
+constexpr int kStrokeMaxPlanes = 57;  // with its halo, a slab's planes fit the lanes of a wavefront
+constexpr int kDownX = 57;  // columns of a down-stroke tile (19 aggregates)
+constexpr int kUpX = 60;    // columns of an up-stroke tile
+
+// x = the degree-2 Chebyshev iterate from zero; fc = P^T (f - A x), fd (nullable) = D^-1 fc.
+template <typename T, bool SYM, int W>
+__global__ void __launch_bounds__(64 * W) k_stroke_down(StrokeView<T> v, CoarseBox<T> cb,
+                                                       const T* __restrict__ f,
+                                                       T* __restrict__ xo, T* __restrict__ fc,
+                                                       T* __restrict__ fd, T c1, T c2, T c20,
+                                                       T omega) {
+    __shared__ T sh[2][3][W + 2][2][64];
+    __shared__ int ring[W][3][3][64];
+    const double skip = v.skip ? *v.skip : 0.0;  // tested once the first loads are on their way
+    int tx, ty, sz;
+    stroke_tile(v, &tx, &ty, &sz);
+    const int lane = threadIdx.x, w = __builtin_amdgcn_readfirstlane(threadIdx.y);
+    const int x = kDownX * tx - 3 + lane;
+    const int yb = 3 * ((W - 2) * ty + w - 1);
+    const int zs = sz * v.S, ze = min(zs + v.S, 3 * cb.mz);
+    const int p0 = zs - 3;
+    const bool own = w > 0 && w < W - 1;  // not a halo wavefront
+    const bool useful = own && lane >= 3 && lane < 3 + kDownX;
+    for (int i = lane + 64 * w; i < 2 * 3 * (W + 2) * 2 * 64; i += 64 * W) (&sh[0][0][0][0][0])[i] = T(0);
+
+    Rows<T, !SYM> rows;
+    rows.ring = &ring[w][0][0][0];
+    rows.init(v, yb, p0);
+    T F[3][3], X[3][3], R[3][3];
+    T nf[3][3];  // the planes in flight, by plane mod 3
+    unsigned lo[3], so[3];  // byte offsets of the lane's nodes in a plane, for loads and stores
+#pragma unroll
+    for (int l = 0; l < 3; ++l) {
+        const bool in = (unsigned)x < (unsigned)v.nx && (unsigned)(yb + l) < (unsigned)v.ny;
+        lo[l] = in ? (unsigned)(v.nx * (yb + l) + x) * (unsigned)sizeof(T) : kOff;
+        so[l] = useful ? lo[l] : kOff;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) F[k][l] = X[k][l] = R[k][l] = T(0);
+    }
+    const int pb = (int)(v.nxy * (long)sizeof(T));  // bytes of a plane
+    const T* pf = f + v.nxy * p0;
+    T* px = xo + v.nxy * (p0 - 1);
+    auto load = [&](int z, T(&d)[3]) {
+        const auto pl = plane(pf, pb, (unsigned)z < (unsigned)v.nz);
+        pf += v.nxy;
+#pragma unroll
+        for (int l = 0; l < 3; ++l) bload(pl, lo[l], d[l]);
+    };
+#pragma unroll
+    for (int k = 0; k < 3; ++k) load(p0 + k, nf[k]);
+    const bool live = rows.preload(v, x, yb, p0, ze + 2 - p0, __ballot(useful));
+    if (skip != 0.0) return;  // the whole grid
+    if (!__syncthreads_or(live)) return;  // no unknown: x and fc are zero there already
+    T acc = T(0);
+    auto step_as = [&](auto ph, auto fast, int p, int buf) {
+        constexpr int A = decltype(ph)::value, B = (A + 2) % 3, C = (A + 1) % 3;
+        constexpr bool FAST = decltype(fast)::value;
+        const int i = p - p0;
+        T(*wr)[W + 2][2][64] = sh[buf];
+        T(*rd)[W + 2][2][64] = sh[buf ^ 1];
+        T yl[3], yh[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            yl[k] = rd[k][w][1][lane];
+            yh[k] = rd[k][w + 2][0][lane];
+        }
+#pragma unroll
+        for (int l = 0; l < 3; ++l) F[A][l] = here(nf[A][l]);
+        load(p + 3, nf[A]);
+        // x on plane p - 1
+        if (!rows.template at<FAST>(v, x, yb, p0, i - 1)) {
+#pragma unroll
+            for (int l = 0; l < 3; ++l) X[B][l] = T(0);
+        } else {
+            const int q = p - 1;
+            const auto pl = plane(px, pb, q >= zs && q < ze && q < v.nz);
+            T af[3];
+            apply3<T>(rows.c.a, F[B], F[C], F[A], yl[0], yh[0], af);
+#pragma unroll
+            for (int l = 0; l < 3; ++l) {
+                const T x1 = c20 * F[B][l];
+                const T d = c1 * x1 + c2 * (F[B][l] - c20 * af[l]);
+                X[B][l] = x1 + d;
+                bstore(pl, so[l], X[B][l]);
+            }
+        }
+        px += v.nxy;
+        // r = f - A x on plane p - 2
+        if (!rows.template at<FAST>(v, x, yb, p0, i - 2)) {
+#pragma unroll
+            for (int l = 0; l < 3; ++l) R[C][l] = T(0);
+        } else {
+            T ax[3];
+            apply3<T>(rows.c.a, X[C], X[A], X[B], yl[1], yh[1], ax);
+#pragma unroll
+            for (int l = 0; l < 3; ++l) R[C][l] = F[C][l] - ax[l];
+        }
+        wr[0][w + 1][0][lane] = F[A][0];
+        wr[0][w + 1][1][lane] = F[A][2];
+        wr[1][w + 1][0][lane] = X[B][0];
+        wr[1][w + 1][1][lane] = X[B][2];
+        wr[2][w + 1][0][lane] = R[C][0];
+        wr[2][w + 1][1][lane] = R[C][2];
+        // r - w A^T r on plane p - 3, summed over the aggregate's three planes and lines
+        if (own && (FAST || i >= 6)) {
+            if (rows.template at<FAST>(v, x, yb, p0, i - 3)) {
+                T ar[3];
+                if constexpr (SYM)
+                    apply3<T>(rows.c.a, R[A], R[B], R[C], yl[2], yh[2], ar);
+                else
+                    apply3<T>(rows.c.at, R[A], R[B], R[C], yl[2], yh[2], ar);
+#pragma unroll
+                for (int l = 0; l < 3; ++l) acc += R[A][l] - omega * ar[l];
+            }
+            if (A == 2) {
+                const T s1 = shift0<false>(acc);
+                const T s = acc + s1 + shift0<false>(s1);
+                acc = T(0);
+                const int X_ = x / 3, Y_ = yb / 3, Z_ = (p - 3) / 3;
+                if (lane >= 3 && lane < 3 + kDownX && lane % 3 == 0 && X_ < cb.mx && Y_ < cb.my) {
+                    const long k = (X_ + 1) + cb.sx * (Y_ + 1) + cb.sxy * (Z_ + 1);
+                    fc[k] = s;
+                    if (fd) fd[k] = cb.invD[k] * s;
+                }
+            }
+        }
+        step_barrier();
+    };
+    const uint64_t steady = rows.steady(1) & ~63ull;
+    auto step = [&](auto ph, int p, int buf) {
+        if ((steady >> (p - p0)) & 1ull)
+            step_as(ph, std::true_type{}, p, buf);
+        else
+            step_as(ph, std::false_type{}, p, buf);
+    };
+    int buf = 0;
+    for (int p = p0; p < ze + 3; p += 3) {  // p0 and ze are multiples of 3
+        step(std::integral_constant<int, 0>{}, p, buf);
+        step(std::integral_constant<int, 1>{}, p + 1, buf ^ 1);
+        step(std::integral_constant<int, 2>{}, p + 2, buf);
+        buf ^= 1;
+    }
+}
+
+// x' = x + P v, two Chebyshev steps on it, out = the result and partials of f . out.
+template <typename T, int W>
+__global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2)))
+k_stroke_up(StrokeView<T> v, CoarseBox<T> cb,
+                                                     const T* __restrict__ vc,
+                                                     const T* __restrict__ xi,
+                                                     const T* __restrict__ f, T* __restrict__ out,
+                                                     T c1, T c2, T c20, T omega, double* part) {
+    __shared__ T sh[2][2][W + 2][2][64];
+    __shared__ int ring[W][3][3][64];
+    __shared__ double lds[W];
+    const double skip = v.skip ? *v.skip : 0.0;
+    int tx, ty, sz;
+    stroke_tile(v, &tx, &ty, &sz);
+    const int lane = threadIdx.x, w = __builtin_amdgcn_readfirstlane(threadIdx.y);
+    const int x = kUpX * tx - 2 + lane;
+    const int yb = 3 * ((W - 2) * ty + w - 1);
+    const int zs = sz * v.S, ze = min(zs + v.S, v.nz);
+    const int p0 = zs - 2;
+    const bool own = w > 0 && w < W - 1;
+    for (int i = lane + 64 * w; i < 2 * 2 * (W + 2) * 2 * 64; i += 64 * W) (&sh[0][0][0][0][0])[i] = T(0);
+
+    Rows<T, false> rows;
+    rows.ring = &ring[w][0][0][0];
+    rows.init(v, yb, p0);
+    T F[3][3], XP[3][3], X1[3][3];
+    T nf[3][3], nx_[3][3];  // the planes in flight, by plane mod 3
+    unsigned lo[3], so[3];
+#pragma unroll
+    for (int l = 0; l < 3; ++l) {
+        const bool in = (unsigned)x < (unsigned)v.nx && (unsigned)(yb + l) < (unsigned)v.ny;
+        lo[l] = in ? (unsigned)(v.nx * (yb + l) + x) * (unsigned)sizeof(T) : kOff;
+        so[l] = lane >= 2 && lane < 2 + kUpX ? lo[l] : kOff;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) F[k][l] = XP[k][l] = X1[k][l] = T(0);
+    }
+    const int pb = (int)(v.nxy * (long)sizeof(T));  // bytes of a plane
+    const T *pf = f + v.nxy * p0, *px = xi + v.nxy * p0;
+    T* po = out + v.nxy * (p0 - 2);
+    auto load = [&](int z, T(&df)[3], T(&dx)[3]) {
+        const bool ok = (unsigned)z < (unsigned)v.nz;
+        const auto bf = plane(pf, pb, ok), bx = plane(px, pb, ok);
+        pf += v.nxy;
+        px += v.nxy;
+#pragma unroll
+        for (int l = 0; l < 3; ++l) {
+            bload(bf, lo[l], df[l]);
+            bload(bx, lo[l], dx[l]);
+        }
+    };
+    // coarse values of the lane's aggregate on layers K - 1, K, K + 1, of the aggregate rows
+    // before and after on layer K, and of the x-neighbour beyond the wavefront (lanes 0, 63)
+    const int J = yb / 3;  // yb is a multiple of 3, at least -3
+    auto col = [&](int xx, int j) {
+        const int X_ = xx < 0 ? 0 : min(xx / 3, cb.mx) + 1;
+        const int Y_ = min(max(j + 1, 0), cb.my + 1);
+        return (unsigned)(X_ + (int)cb.sx * Y_);
+    };
+    const unsigned o0 = col(x, J), om = col(x, J - 1), op = col(x, J + 1),
+                   oe = col(lane == 0 ? x - 1 : x + 1, J);
+    auto layer = [&](int k) { return vc + cb.sxy * min(max(k + 1, 0), cb.mz + 1); };
+    int K = zs / 3 - 1;  // layer of plane zs - 2
+    T vm = T(0), v0 = layer(K)[o0], vp = layer(K + 1)[o0];
+    T vym = layer(K)[om], vyp = layer(K)[op], ve = layer(K)[oe];
+    T nvp, nym, nyp, nve;
+    auto next_layer = [&]() {
+        nvp = layer(K + 2)[o0];
+        const T* l1 = layer(K + 1);
+        nym = l1[om];
+        nyp = l1[op];
+        nve = l1[oe];
+    };
+    next_layer();
+#pragma unroll
+    for (int k = 0; k < 3; ++k) load(p0 + k, nf[(k + 1) % 3], nx_[(k + 1) % 3]);
+    const bool live = rows.preload(v, x, yb, p0, ze + 2 - p0,
+                                   __ballot(own && lane >= 2 && lane < 2 + kUpX));
+    if (skip != 0.0) return;
+    if (!__syncthreads_or(live)) {
+        if (part && lane == 0 && w == 0) part[blockIdx.x] = 0.0;
+        return;
+    }
+    double dsum = 0.0;
+    // zeros where the node of plane z is not an unknown
+    auto mask_z = [&](int z, T(&e)[3]) {
+#pragma unroll
+        for (int l = 0; l < 3; ++l) {
+            uint64_t u = 0;
+            if ((unsigned)z < (unsigned)v.nz && lo[l] != kOff)
+                u = v.unk[((long)z * v.ny + yb + l) * v.nsegx + (x >> 6)] >> (x & 63);
+            e[l] = u & 1ull ? e[l] : T(0);
+        }
+        settle(e);
+    };
+    auto step_as = [&](auto ph, auto fast, int p, int buf) {
+        constexpr int A = decltype(ph)::value, B = (A + 2) % 3, C = (A + 1) % 3;
+        constexpr bool FAST = decltype(fast)::value;
+        const int i = p - p0;
+        T(*wr)[W + 2][2][64] = sh[buf];
+        T(*rd)[W + 2][2][64] = sh[buf ^ 1];
+        T yl[2], yh[2];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            yl[k] = rd[k][w][1][lane];
+            yh[k] = rd[k][w + 2][0][lane];
+        }
+        T xin[3];
+#pragma unroll
+        for (int l = 0; l < 3; ++l) {
+            F[A][l] = here(nf[A][l]);
+            xin[l] = here(nx_[A][l]);
+        }
+        if (A == 0) {  // the next layer of aggregates
+            ++K;
+            vm = v0;
+            v0 = vp;
+            vp = nvp;
+            vym = nym;
+            vyp = nyp;
+            ve = nve;
+            next_layer();
+        }
+        load(p + 3, nf[A], nx_[A]);
+        if (!rows.template at<FAST>(v, x, yb, p0, i)) {
+#pragma unroll
+            for (int l = 0; l < 3; ++l) XP[A][l] = T(0);
+        } else {
+            const T xm = wave_shift<true>(v0, ve), xp = wave_shift<false>(v0, ve);
+            T zm[3], zp[3];
+#pragma unroll
+            for (int l = 0; l < 3; ++l) {
+                zm[l] = A == 0 ? vm : v0;
+                zp[l] = A == 2 ? vp : v0;
+            }
+            // P v is zero off the unknowns.  Rows hold zeros towards neighbours in x and y that
+            // are none, but along z they may stand for several planes: where the line changes
+            // from plane to plane its neighbours are masked
+            if (!FAST && ((rows.change >> i) & 3ull)) {
+                mask_z(p - 1, zm);
+                mask_z(p + 1, zp);
+            }
+#pragma unroll
+            for (int l = 0; l < 3; ++l) {
+                const T ym = l ? v0 : vym, yp = l < 2 ? v0 : vyp;
+                const T(&a)[6] = rows.c.a[l];
+                const T ae = v0 + a[0] * xm + a[1] * xp + a[2] * ym + a[3] * yp + a[4] * zm[l] +
+                             a[5] * zp[l];
+                const T o = xin[l] + (v0 - omega * ae);
+                XP[A][l] = (rows.c.um[l] >> lane) & 1ull ? o : T(0);
+            }
+        }
+        if (!rows.template at<FAST>(v, x, yb, p0, i - 1)) {
+#pragma unroll
+            for (int l = 0; l < 3; ++l) X1[B][l] = T(0);
+        } else {
+            T ax[3];
+            apply3<T>(rows.c.a, XP[B], XP[C], XP[A], yl[0], yh[0], ax);
+#pragma unroll
+            for (int l = 0; l < 3; ++l) X1[B][l] = XP[B][l] + c20 * (F[B][l] - ax[l]);
+        }
+        wr[0][w + 1][0][lane] = XP[A][0];
+        wr[0][w + 1][1][lane] = XP[A][2];
+        wr[1][w + 1][0][lane] = X1[B][0];
+        wr[1][w + 1][1][lane] = X1[B][2];
+        if (own && (FAST || i >= 4) && rows.template at<FAST>(v, x, yb, p0, i - 2)) {
+            T ax[3];
+            apply3<T>(rows.c.a, X1[C], X1[A], X1[B], yl[1], yh[1], ax);
+            const auto pl = plane(po, pb, true);
+#pragma unroll
+            for (int l = 0; l < 3; ++l) {
+                const T d = c1 * (X1[C][l] - XP[C][l]) + c2 * (F[C][l] - ax[l]);
+                const T z = X1[C][l] + d;
+                bstore(pl, so[l], z);
+                dsum += so[l] != kOff ? (double)F[C][l] * (double)z : 0.0;
+            }
+        }
+        po += v.nxy;
+        step_barrier();
+    };
+    const uint64_t steady = rows.steady(0) & ~(rows.change >> 1) & ~15ull;
+    auto step = [&](auto ph, int p, int buf) {
+        if ((steady >> (p - p0)) & 1ull)
+            step_as(ph, std::true_type{}, p, buf);
+        else
+            step_as(ph, std::false_type{}, p, buf);
+    };
+    int buf = 0;
+    for (int p = p0; p < ze + 2; p += 3) {  // p0 = 1 mod 3
+        step(std::integral_constant<int, 1>{}, p, buf);
+        if (p + 1 < ze + 2) step(std::integral_constant<int, 2>{}, p + 1, buf ^ 1);
+        if (p + 2 < ze + 2) step(std::integral_constant<int, 0>{}, p + 2, buf);
+        buf ^= 1;
+    }
+    const double s = block_sum(dsum, lds);
+    if (part && lane == 0 && w == 0) part[blockIdx.x] = s;
+}
+
+// ---- what the strokes know of each line
+//
+// The rows of a line (y, z) may stand for those of the line one plane below when both have
+// the same unknowns and, at every unknown, rows that agree in each coefficient whose
+// neighbour is an unknown of both lines' surroundings: along z the end planes of a pipe
+// lack a neighbour, whose coefficient is free because the value there is zero.  A pipe of
+// constant cross-section is then one group from end to end.  The rows of a group are read
+// from one of its planes that has both z-neighbours: the plane itself, the one above the
+// group's first, or the one below its last.  A group of two planes has none and is split.
+
+// One wavefront per line: compat[y][z] = 1 where the rows of (y, z - 1) may stand for
+// (y, z)'s, and 2 where the line has an unknown.
+__global__ void __launch_bounds__(kThreads) k_zcompat(L0View<double> v, uint8_t* __restrict__ compat) {
+    const long line = (long)blockIdx.x * kBlockY + threadIdx.y;
+    if (line >= (long)v.ny * v.nz) return;
+    const int lane = threadIdx.x, z = (int)(line / v.ny), y = (int)(line % v.ny);
+    const long step = (long)v.ny * v.nsegx;
+    bool ok = true, any = false;
+    for (int q = 0; q < v.nsegx; ++q) {
+        const long s1 = line * v.nsegx + q, s0 = s1 - step;
+        const uint64_t u = v.unk[s1];
+        any = any || u != 0;
+        if (z == 0) {
+            ok = ok && u == 0;
+            continue;
+        }
+        if (u != v.unk[s0]) {
+            ok = false;
+            continue;
+        }
+        const uint64_t r1 = v.irr[s1], r0 = v.irr[s0];
+        if (u == 0 || (r1 == r0 && (r1 == 0 || v.base[s1] == v.base[s0]))) continue;
+        // whether the z-neighbours beyond the pair are unknowns
+        const bool below = z >= 2 && ((v.unk[s0 - step] >> lane) & 1ull);
+        const bool above = z + 1 < v.nz && ((v.unk[s1 + step] >> lane) & 1ull);
+        bool same = true;
+        if ((u >> lane) & 1ull) {
+            const uint64_t m = (1ull << lane) - 1ull;
+            const bool i1 = (r1 >> lane) & 1ull, i0 = (r0 >> lane) & 1ull;
+            const long k1 = v.base[s1] + (int)__popcll(r1 & m), k0 = v.base[s0] + (int)__popcll(r0 & m);
+            for (int d = 0; d < 6; ++d) {
+                if ((d == 4 && !below) || (d == 5 && !above)) continue;
+                const double c = v.c[d >> 1];
+                const double a1 = i1 ? v.tcoef(d, k1) : c, a0 = i0 ? v.tcoef(d, k0) : c;
+                const double t1 = i1 ? v.tcoefT(d, k1) : c, t0 = i0 ? v.tcoefT(d, k0) : c;
+                same = same && a1 == a0 && t1 == t0;
+            }
+        }
+        if (__ballot(!same) != 0) ok = false;
+    }
+    if (lane == 0) compat[(long)v.nz * y + z] = (ok ? 1 : 0) | (any ? 2 : 0);
+}
+
+// zinfo[y][z], z = 0..nz: kZSame where the line's rows are those of the line below, kZUnk
+// where it has an unknown, and from bit kZRep 1 + (the plane its rows are read from - z).
+__global__ void __launch_bounds__(256) k_zinfo(int ny, int nz, const uint8_t* __restrict__ compat,
+                                               uint8_t* __restrict__ zinfo) {
+    const long t = blockIdx.x * 256L + threadIdx.x;
+    if (t >= (long)ny * (nz + 1)) return;
+    const int y = (int)(t / (nz + 1)), z = (int)(t % (nz + 1));
+    const uint8_t* c = compat + (long)nz * y;
+    if (z == nz) {  // above the box: as an empty line
+        zinfo[t] = ((c[nz - 1] & 2) ? 0 : kZSame) | (1 << kZRep);
+        return;
+    }
+    auto same = [&](int k) { return k >= 0 && k < nz && (c[k] & 1); };  // plane k continues a group
+    bool s = same(z);
+    int rep = 0;
+    if (s && !same(z - 1) && !same(z + 1)) {
+        s = false;  // the second of two planes
+    } else if (s && !same(z + 1)) {
+        rep = -1;  // the last of at least three
+    } else if (!s && same(z + 1) && same(z + 2)) {
+        rep = 1;  // the first of at least three
+    }
+    zinfo[t] = (s ? kZSame : 0) | ((c[z] & 2) ? kZUnk : 0) | ((1 + rep) << kZRep);
+}
+
+long zinfo_bytes(const FineLevel& L) { return (long)L.ny * (L.nz + 1); }
+
+static StrokeTile stroke_tiling(const FineLevel& L, const std::vector<uint64_t>& shadow, bool up,
+                                int bytes, std::vector<int32_t>* tiles);
+
+// Which nodes of the (x, y) cross-section hold an unknown on any plane: OR of the unknown
+// masks over z, 32 planes a thread.
+__global__ void __launch_bounds__(256) k_shadow(int nz, long words, const uint64_t* __restrict__ unk,
+                                                uint64_t* __restrict__ shadow) {
+    const long t = blockIdx.x * 256L + threadIdx.x;
+    if (t >= words) return;
+    uint64_t m = 0;
+    const int z1 = min(nz, 32 * (int)(blockIdx.y + 1));
+    for (int z = 32 * blockIdx.y; z < z1; ++z) m |= unk[words * z + t];
+    if (m) atomicOr((unsigned long long*)&shadow[t], (unsigned long long)m);
+}
+
+void l0_zinfo(FineLevel& L, hipStream_t s) {
+    if (!L.zinfo) L.zinfo = (uint8_t*)dmalloc(zinfo_bytes(L));
+    const long lines = (long)L.ny * L.nz;
+    Tmp compat(lines);
+    hipLaunchKernelGGL(k_zcompat, dim3((unsigned)((lines + kBlockY - 1) / kBlockY)),
+                       dim3(kWave, kBlockY), 0, s, L.view<double>(), compat.as<uint8_t>());
+    hipLaunchKernelGGL(k_zinfo, dim3((unsigned)((zinfo_bytes(L) + 255) / 256)), dim3(256), 0, s,
+                       L.ny, L.nz, (const uint8_t*)compat.as<uint8_t>(), L.zinfo);
+    HIPCHECK(hipGetLastError());
+    if (L.stroke[0][0].W != 0) return;  // the unknowns never change
+    const long words = (long)L.ny * L.nsegx;
+    Tmp sh(8 * words);
+    std::vector<uint64_t> shadow(words);
+    hipLaunchKernelGGL(k_shadow, dim3((unsigned)((words + 255) / 256), (unsigned)((L.nz + 31) / 32)),
+                       dim3(256), 0, s, L.nz, words, (const uint64_t*)L.unk, sh.as<uint64_t>());
+    HIPCHECK(hipGetLastError());
+    HIPCHECK(hipMemcpyAsync(shadow.data(), sh.p, 8 * words, hipMemcpyDeviceToHost, s));
+    HIPCHECK(hipStreamSynchronize(s));
+    std::vector<int32_t> lists;
+    for (int d = 0; d < 2; ++d)
+        for (int up = 0; up < 2; ++up) {
+            std::vector<int32_t> tiles;
+            StrokeTile& t = L.stroke[d][up];
+            t = stroke_tiling(L, shadow, up != 0, d ? 8 : 4, &tiles);
+            t.list = (int)lists.size();
+            lists.insert(lists.end(), tiles.begin(), tiles.end());
+        }
+    L.tiles = (int32_t*)dmalloc(4 * lists.size());
+    HIPCHECK(hipMemcpyAsync(L.tiles, lists.data(), 4 * lists.size(), hipMemcpyHostToDevice, s));
+    HIPCHECK(hipStreamSynchronize(s));  // the host list goes
+}
+
+// The tiles of the cross-section that hold an unknown.
+static std::vector<int32_t> live_tiles(const FineLevel& L, const std::vector<uint64_t>& shadow,
+                                       int tx, int lines) {
+    std::vector<int32_t> out;
+    for (int j = 0; j * lines < L.ny; ++j)
+        for (int i = 0; i * tx < L.nx; ++i) {
+            const int x0 = i * tx, x1 = std::min(L.nx, x0 + tx), y1 = std::min(L.ny, lines * (j + 1));
+            bool any = false;
+            for (int y = lines * j; y < y1 && !any; ++y)
+                for (int q = x0 >> 6; q <= (x1 - 1) >> 6 && !any; ++q) {
+                    uint64_t m = shadow[(long)y * L.nsegx + q];
+                    if (x0 > 64 * q) m &= ~0ull << (x0 - 64 * q);
+                    if (x1 < 64 * q + 64) m &= ~0ull >> (64 * q + 64 - x1);
+                    any = m != 0;
+                }
+            if (any) out.push_back(i | (j << 16));
+        }
+    return out;
+}
+
+// Tile of a stroke: wavefronts per block and planes per slab.  More wavefronts re-read and
+// recompute fewer halo lines (3 W - 6 of 3 W are outputs) and longer slabs fewer halo planes,
+// while a launch whose last round of blocks is nearly empty, or that leaves compute units
+// without work, loses more than the halo: the choice minimises a model of the time,
+//   start + (S + halo) sum over rounds of (a + b n),
+// with n wavefronts per SIMD and the blocks that hold unknowns.  a and b are the microseconds
+// of a plane step measured on boxes from 33^3 to 256 x 256 x 768 (fp32, 8 wavefronts a block:
+// 0.79 us with one block on a compute unit, 1.18 with two; fp64: 0.50 with one wavefront per
+// SIMD, 0.87 with two).  On a 128 x 128 x 256 box in fp64 (down / up): 27 planes (240 blocks)
+// 31.4 / 37.6 us, 24 planes (264 blocks, 8 of them in a second round) 51.9 / 61.9 us, 12 planes
+// 52.4 / 62.8 us; on the 256 x 256 x 768 ellipse in fp32 with 16 wavefronts 48 planes 169 / 204
+// us, 24 planes 177 / 215, 54 planes 193 / 236.
+static StrokeTile stroke_tiling(const FineLevel& L, const std::vector<uint64_t>& shadow, bool up,
+                                int bytes, std::vector<int32_t>* tiles) {
+    const int tx = up ? kUpX : kDownX;
+    StrokeTile best;
+    double t_best = 0.0;
+    for (int W : {4, 8, 16}) {
+        if (bytes == 8 && W == 16) break;  // fp64: 128 registers a lane do not hold the state
+        const int per_cu = (bytes == 4 ? 16 : 8) / W;  // blocks that fit a compute unit's registers
+        const double a = bytes == 4 ? 0.38 : 0.15, b = bytes == 4 ? 0.20 : 0.36;
+        const std::vector<int32_t> list = live_tiles(L, shadow, tx, 3 * (W - 2));
+        StrokeTile t;
+        t.W = W;
+        t.live = (int)list.size();
+        bool better = false;
+        for (t.S = 3; t.S <= kStrokeMaxPlanes; t.S += 3) {
+            t.gz = (L.nz + t.S - 1) / t.S;
+            const long slots = 256L * per_cu, full = t.blocks() / slots, rest = t.blocks() % slots;
+            const double n1 = (double)W / 4;  // wavefronts per SIMD of one block
+            double round = full * (a + b * n1 * per_cu);
+            if (rest) round += a + b * n1 * ((rest + 255) / 256);
+            const double us = 4.0 + (t.S + 6) * round;
+            if (best.W == 0 || us < t_best) {
+                best = t;
+                t_best = us;
+                better = true;
+            }
+        }
+        if (better) *tiles = list;
+    }
+    return best;
+}
+
+template <typename T>
+static StrokeView<T> stroke_view(const FineLevel& L, const StrokeTile& t) {
+    const L0View<T> l = L.view<T>();
+    StrokeView<T> v;
+    v.nx = L.nx; v.ny = L.ny; v.nz = L.nz; v.nsegx = L.nsegx; v.nxy = L.nxy;
+    v.unk = l.unk; v.irr = l.irr; v.base = l.base; v.tab = l.tab; v.tabT = l.tabT;
+    for (int a = 0; a < 3; ++a) v.c[a] = l.c[a];
+    v.zinfo = L.zinfo;
+    v.tiles = L.tiles + t.list;
+    v.live = t.live;
+    v.S = t.S;
+    v.skip = l.skip;
+    return v;
+}
+
+template <typename T>
+static CoarseBox<T> coarse_box(const CoarseLevel& C) {
+    CoarseBox<T> b;
+    b.mx = C.mx; b.my = C.my; b.mz = C.mz;
+    b.sx = C.sx; b.sxy = C.sxy;
+    b.invD = sizeof(T) == 8 ? (const T*)C.invD64 : (const T*)C.invD32;
+    return b;
+}
+
+// Strokes need the degree-2 smoother and planes that a 32-bit byte offset reaches.
+bool l0_strokes(const FineLevel& L, int degree, int bytes) {
+    return degree == 2 && L.nxy * bytes < (long)kOff;
+}
+
+long l0_stroke_parts(const FineLevel& L, int bytes) { return L.stroke[bytes == 8][1].blocks(); }
+
+// Bytes of a stroke: level-0 vectors it reads or writes, the coarse vector, and per line the
+// z-information (masks and table rows only where a line changes along z).
+static long stroke_bytes(const FineLevel& L, const CoarseLevel& C, int vecs, int coarse, long w) {
+    return (vecs * L.n_unknowns + coarse * C.n_unknowns) * w + zinfo_bytes(L);
+}
+
+template <typename T>
+void l0_down(const FineLevel& L, const CoarseLevel& C, bool sym, const T* f, T* x, T* fc, T* fd,
+             double c1, double c2, double c20, double omega, hipStream_t s) {
+    const StrokeTile& t = L.stroke[sizeof(T) == 8][0];
+    const StrokeView<T> v = stroke_view<T>(L, t);
+    const CoarseBox<T> cb = coarse_box<T>(C);
+    const dim3 g((unsigned)t.blocks()), b(kWave, t.W);
+    const long by = stroke_bytes(L, C, 2, fd ? 3 : 1, sizeof(T));
+    KTimer kt(s, {{T_L0_CHEB, by / 3}, {T_L0_RESID, by / 3}, {T_L0_RESTRICT, by / 3}});
+#define DOWN(W_, SYM_)                                                                         \
+    klaunch(kt, true, (k_stroke_down<T, SYM_, W_>), g, b, v, cb, f, x, fc, fd, (T)c1, (T)c2,    \
+            (T)c20, (T)omega)
+    if (t.W == 4 && sym) DOWN(4, true);
+    else if (t.W == 4) DOWN(4, false);
+    else if (t.W == 8 && sym) DOWN(8, true);
+    else if (t.W == 8) DOWN(8, false);
+    else if constexpr (sizeof(T) == 4) {
+        if (sym) DOWN(16, true);
+        else DOWN(16, false);
+    }
+#undef DOWN
+    HIPCHECK(hipGetLastError());
+}
+template void l0_down<double>(const FineLevel&, const CoarseLevel&, bool, const double*, double*,
+                              double*, double*, double, double, double, double, hipStream_t);
+template void l0_down<float>(const FineLevel&, const CoarseLevel&, bool, const float*, float*,
+                             float*, float*, double, double, double, double, hipStream_t);
+
+template <typename T>
+void l0_up(const FineLevel& L, const CoarseLevel& C, const T* vc, const T* x, const T* f, T* out,
+           double c1, double c2, double c20, double omega, double* dot, hipStream_t s) {
+    const StrokeTile& t = L.stroke[sizeof(T) == 8][1];
+    const StrokeView<T> v = stroke_view<T>(L, t);
+    const CoarseBox<T> cb = coarse_box<T>(C);
+    const dim3 g((unsigned)t.blocks()), b(kWave, t.W);
+    const long by = stroke_bytes(L, C, 3, 1, sizeof(T));
+    KTimer kt(s, {{T_L0_PROLONG, by / 3}, {T_L0_CHEB, by / 3 * 2}});
+#define UP(W_)                                                                                 \
+    klaunch(kt, true, (k_stroke_up<T, W_>), g, b, v, cb, vc, x, f, out, (T)c1, (T)c2, (T)c20,   \
+            (T)omega, dot)
+    if (t.W == 4) UP(4);
+    else if (t.W == 8) UP(8);
+    else if constexpr (sizeof(T) == 4) UP(16);
+#undef UP
+    HIPCHECK(hipGetLastError());
+}
+template void l0_up<double>(const FineLevel&, const CoarseLevel&, const double*, const double*,
+                            const double*, double*, double, double, double, double, double*,
+                            hipStream_t);
+template void l0_up<float>(const FineLevel&, const CoarseLevel&, const float*, const float*,
+                           const float*, float*, double, double, double, double, double*,
+                           hipStream_t);
+
+}  // namespace saamg

@@ -11,8 +11,9 @@ constexpr int kMaxSlots = 65536;
 
 struct Slot {
     hipEvent_t a = nullptr, b = nullptr;
-    int kind = 0;
-    long units = 0;
+    long units[T_NKIND] = {};  // of the classes that count the launch (bit of `kinds`)
+    unsigned kinds = 0;
+    long all = 0;              // units of every class of the launch, counted or not
 };
 
 struct Timers {
@@ -29,9 +30,13 @@ Timers& timers() {
 
 }  // namespace
 
-KTimer::KTimer(int k, hipStream_t st, long units) : kind(k), s(st) {
+KTimer::KTimer(int k, hipStream_t st, long units) : KTimer(st, {{k, units}}) {}
+
+KTimer::KTimer(hipStream_t st, std::initializer_list<std::pair<int, long>> classes) : s(st) {
     Timers& T = timers();
-    if (!T.enabled[k]) return;
+    bool on = false;
+    for (auto& c : classes) on = on || T.enabled[c.first];
+    if (!on) return;
     std::lock_guard<std::mutex> g(T.mu);
     if (T.used >= kMaxSlots) return;
     if ((int)T.slots.size() <= T.used) {
@@ -40,8 +45,14 @@ KTimer::KTimer(int k, hipStream_t st, long units) : kind(k), s(st) {
         T.slots.push_back(sl);
     }
     slot = T.used++;
-    T.slots[slot].kind = k;
-    T.slots[slot].units = units;
+    Slot& sl = T.slots[slot];
+    sl.kinds = 0;
+    sl.all = 0;
+    for (auto& c : classes) {
+        sl.units[c.first] = c.second;
+        sl.all += c.second;
+        if (T.enabled[c.first]) sl.kinds |= 1u << c.first;
+    }
 }
 
 hipEvent_t KTimer::start() {
@@ -81,13 +92,14 @@ int saamg_timer_read(int kind, double* total_ms, int64_t* launches, int64_t* uni
     int64_t n = 0, u = 0;
     for (int i = 0; i < T.used; ++i) {
         auto& sl = T.slots[i];
-        if (sl.kind != kind) continue;
+        if (!((sl.kinds >> kind) & 1u)) continue;
         if (hipEventSynchronize(sl.b) != hipSuccess) return SAAMG_HIP_ERROR;
         float e = 0.f;
         if (hipEventElapsedTime(&e, sl.a, sl.b) != hipSuccess) return SAAMG_HIP_ERROR;
-        ms += e;
+        const long own = sl.units[kind];
+        ms += own == sl.all ? e : e * ((double)own / (double)sl.all);
         ++n;
-        u += sl.units;
+        u += own;
     }
     if (total_ms) *total_ms = ms;
     if (launches) *launches = n;
