@@ -608,6 +608,252 @@ template void lc_prolong<double>(const CoarseLevel&, const CoarseLevel&, const d
 template void lc_prolong<float>(const CoarseLevel&, const CoarseLevel&, const float*, float*,
                                 double, hipStream_t);
 
+// ================================================================ strokes of levels >= 1
+//
+// The degree-2 V-cycle of a level in two launches, as on level 0 (stroke.hip): down = the
+// zero-guess smoothing, the residual and the restriction; up = the prolongation and both
+// post-smoothing steps.  A block owns a tile of kLcT^3 nodes (2 x 2 x 2 aggregates) and applies
+// the three stencils one after the other on shrinking boxes around it (halo 2, 1, 0; the
+// vectors in LDS), so that a level costs two launches instead of seven.  The halo is computed
+// again by the neighbouring blocks (1000 + 512 + 216 rows for 216 nodes).  Small levels are
+// bound by a launch's 4.7 us and the dependent loads slot -> table row in each: here they are
+// paid once per stroke, under the staging of the vectors, because a thread keeps its node's row
+// through all stages.  Measured (seven kernels -> two strokes): the 33 x 33 x 97 and 11 x 11 x
+// 33 levels of a 97 x 97 x 291 cavity in fp32 34 -> 16 us each, an 11^3 level in fp64 37 -> 15,
+// a 15 x 15 x 29 level in fp64 39 -> 18.  Large levels are bound by the rows computed, where the
+// step kernels win: 43 x 43 x 86 in fp64 44 -> 54 us, 86 x 86 x 256 in fp32 104 -> 200 us.
+constexpr int kLcT = 6;
+constexpr int kLcE3 = kLcT + 6, kLcE2 = kLcT + 4;  // lines of the boxes with halo 3 and 2
+constexpr int kLcN3 = kLcE3 * kLcE3 * kLcE3, kLcN2 = kLcE2 * kLcE2 * kLcE2;
+constexpr int kLcThreads = 1024;
+
+// The next level as the strokes address it.
+template <typename T>
+struct LcNextOut {
+    int mx, my, mz;
+    long sx, sxy;
+    T* f;
+};
+template <typename T>
+struct LcNextIn {
+    int mx, my, mz;
+    long sx, sxy;
+    const T* v;
+};
+
+struct LcBlocks {
+    int gx, gy, gz;
+    unsigned n() const { return (unsigned)gx * gy * gz; }
+};
+static LcBlocks lc_blocks3(const CoarseLevel& C) {
+    return {(C.mx + kLcT - 1) / kLcT, (C.my + kLcT - 1) / kLcT, (C.mz + kLcT - 1) / kLcT};
+}
+
+// First node of the block's tile (XCD-aware order: each XCD takes a run of tiles along x).
+__device__ __forceinline__ void lc_tile3(const LcBlocks& g, int* X, int* Y, int* Z) {
+    const unsigned b = blockIdx.x, nb = gridDim.x, q = nb >> 3;
+    const unsigned lb = (b < 8 * q) ? (b & 7) * q + (b >> 3) : b;
+    *X = kLcT * (int)(lb % (unsigned)g.gx);
+    *Y = kLcT * (int)(lb / (unsigned)g.gx % (unsigned)g.gy);
+    *Z = kLcT * (int)(lb / (unsigned)(g.gx * g.gy));
+}
+
+// Storage index of the node at (X, Y, Z), or of a ghost node (where every vector and 1/diag
+// is 0 and the slot is -2) for a node outside the level's box: its values can then be loaded
+// like any other's.
+template <typename T>
+__device__ __forceinline__ long lc_at3(const LCView<T>& c, int X, int Y, int Z) {
+    const bool in = (unsigned)X < (unsigned)c.mx && (unsigned)Y < (unsigned)c.my && (unsigned)Z < (unsigned)c.mz;
+    return in ? (X + 1) + (long)c.sx * (Y + 1) + c.sxy * (Z + 1) : 0L;
+}
+
+// The row of slot s in registers (TR: of A^T): the table's, the interior stencil, or zeros.
+template <typename T, bool TR>
+__device__ __forceinline__ void lc_get_row(const LCView<T>& c, int s, T (&t)[kLcRow]) {
+#pragma unroll
+    for (int k = 0; k < 27; ++k) t[k] = s == -1 ? c.cst[TR ? 26 - k : k] : T(0);
+    if (s >= 0) lc_load_row(TR ? c.tbT : c.tb, s, t);
+}
+// sum_k t_k x_k over the node's 27 neighbours in LDS (E nodes a line), in order k = 0..26.
+template <int E, typename T>
+__device__ __forceinline__ T lc_sum27(const T (&t)[kLcRow], const T* xs) {
+    T acc = T(0);
+#pragma unroll
+    for (int k = 0; k < 27; ++k)
+        acc += t[k] * xs[(k % 3 - 1) + E * ((k / 3) % 3 - 1) + E * E * (k / 9 - 1)];
+    return acc;
+}
+
+// Thread t works on node t of the tile's box with halo 2, in every stage that the node takes
+// part in (all; halo 1; the tile), so that its stencil row, right-hand side and 1/diag are
+// read once and stay in registers.
+struct LcMine {
+    int x, y, z;  // in the box with halo 2
+    bool on, h1, own;
+    __device__ __forceinline__ LcMine(int t) {
+        x = t % kLcE2;
+        y = t / kLcE2 % kLcE2;
+        z = t / (kLcE2 * kLcE2);
+        auto within = [&](int h) {
+            return x >= h && x < kLcE2 - h && y >= h && y < kLcE2 - h && z >= h && z < kLcE2 - h;
+        };
+        on = t < kLcN2;
+        h1 = on && within(1);
+        own = on && within(2);
+    }
+};
+
+template <typename T, bool SYM>
+__global__ void __launch_bounds__(kLcThreads) k_lc_down(LCView<T> c, LcBlocks g, const T* __restrict__ f,
+                                                        T* __restrict__ xo, LcNextOut<T> cc, T c1,
+                                                        T c2, T c20, T omega) {
+    __shared__ T sa[kLcN3];  // D^-1 f (halo 3); then D^-1 r (lines of the halo-2 box)
+    __shared__ T sb[kLcN2];  // x; then y
+    const double skip = c.skip ? *c.skip : 0.0;
+    int X0, Y0, Z0;
+    lc_tile3(g, &X0, &Y0, &Z0);
+    const int t = threadIdx.x;
+    const LcMine m(t);
+    const long i = m.on ? lc_at3(c, X0 + m.x - 2, Y0 + m.y - 2, Z0 + m.z - 2) : 0L;
+    const int s = c.slot[i];
+    const T fi = f[i], id = c.invD[i];
+    T fh[2], dh[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const int u = min(t + q * kLcThreads, kLcN3 - 1);
+        const long j = lc_at3(c, X0 + u % kLcE3 - 3, Y0 + u / kLcE3 % kLcE3 - 3, Z0 + u / (kLcE3 * kLcE3) - 3);
+        fh[q] = f[j];
+        dh[q] = c.invD[j];
+    }
+    T row[kLcRow];
+    lc_get_row<T, false>(c, s, row);
+    if (skip != 0.0) return;  // the whole grid, before any barrier
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+        if (t + q * kLcThreads < kLcN3) sa[t + q * kLcThreads] = dh[q] * fh[q];
+    __syncthreads();
+    if (m.on) {
+        const T ax = c20 * lc_sum27<kLcE3>(row, sa + (m.x + 1) + kLcE3 * ((m.y + 1) + kLcE3 * (m.z + 1)));
+        const T x1 = c20 * id * fi;
+        const T x = x1 + (c1 * x1 + c2 * id * (fi - ax));
+        sb[t] = x;
+        if (m.own && i) xo[i] = x;
+    }
+    __syncthreads();
+    T r = T(0);
+    if (m.h1) {
+        r = fi - lc_sum27<kLcE2>(row, sb + t);
+        sa[t] = id * r;
+    }
+    if (!SYM && m.own) lc_get_row<T, true>(c, c.slotT[i], row);
+    __syncthreads();
+    if (m.own) sb[t] = id != T(0) ? r - omega * lc_sum27<kLcE2>(row, sa + t) : T(0);
+    __syncthreads();
+    constexpr int A = kLcT / 3;
+    if (t < A * A * A) {
+        const int a = t % A, b = t / A % A, d = t / (A * A);
+        const int X = X0 / 3 + a, Y = Y0 / 3 + b, Z = Z0 / 3 + d;
+        if (X < cc.mx && Y < cc.my && Z < cc.mz) {
+            const T* y = sb + (3 * a + 2) + kLcE2 * ((3 * b + 2) + kLcE2 * (3 * d + 2));
+            T acc = T(0);
+#pragma unroll
+            for (int q = 0; q < 27; ++q) acc += y[q % 3 + kLcE2 * (q / 3 % 3) + kLcE2 * kLcE2 * (q / 9)];
+            cc.f[(X + 1) + cc.sx * (Y + 1) + cc.sxy * (Z + 1)] = acc;
+        }
+    }
+}
+
+template <typename T>
+__global__ void __launch_bounds__(kLcThreads) k_lc_up(LCView<T> c, LcBlocks g, const T* __restrict__ xi,
+                                                      const T* __restrict__ f, T* __restrict__ xo,
+                                                      LcNextIn<T> cc, T c1, T c2, T c20, T omega) {
+    __shared__ T sa[kLcN3];  // P_tent v (halo 3); then the first step's x (lines of the halo-2 box)
+    __shared__ T sb[kLcN2];  // x + P v
+    const double skip = c.skip ? *c.skip : 0.0;
+    int X0, Y0, Z0;
+    lc_tile3(g, &X0, &Y0, &Z0);
+    const int t = threadIdx.x;
+    const LcMine m(t);
+    const long i = m.on ? lc_at3(c, X0 + m.x - 2, Y0 + m.y - 2, Z0 + m.z - 2) : 0L;
+    const int s = c.slot[i];
+    const T fi = f[i], id = c.invD[i], xv = xi[i];
+    T e[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const int u = min(t + q * kLcThreads, kLcN3 - 1);
+        // the aggregate of the node, in the ghost layer beyond the box
+        const int X = min((X0 + u % kLcE3) / 3, cc.mx + 1), Y = min((Y0 + u / kLcE3 % kLcE3) / 3, cc.my + 1),
+                  Z = min((Z0 + u / (kLcE3 * kLcE3)) / 3, cc.mz + 1);
+        e[q] = cc.v[X + cc.sx * Y + cc.sxy * Z];
+    }
+    T row[kLcRow];
+    lc_get_row<T, false>(c, s, row);
+    if (skip != 0.0) return;
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+        if (t + q * kLcThreads < kLcN3) sa[t + q * kLcThreads] = e[q];
+    __syncthreads();
+    T x = T(0);
+    if (m.on) {
+        const T* p = sa + (m.x + 1) + kLcE3 * ((m.y + 1) + kLcE3 * (m.z + 1));
+        if (id != T(0)) x = xv + (*p - omega * id * lc_sum27<kLcE3>(row, p));
+        sb[t] = x;
+    }
+    __syncthreads();
+    T d = T(0);
+    if (m.h1) {
+        d = c20 * (id * (fi - lc_sum27<kLcE2>(row, sb + t)));
+        x += d;
+        sa[t] = x;
+    }
+    __syncthreads();
+    if (m.own && i) {
+        const T rr = id * (fi - lc_sum27<kLcE2>(row, sa + t));
+        xo[i] = x + (c1 * d + c2 * rr);
+    }
+}
+
+// A stroke's blocks of 1024 threads fit twice on a compute unit in fp32 and once in fp64, and
+// a round of them takes about 6 us; the step kernels march the level seven times at no less
+// than 4.7 us each.  The two meet near 250 thousand nodes in fp32 and 140 thousand in fp64.
+bool lc_strokes(const CoarseLevel& C, int degree, int bytes) {
+    return degree == 2 && lc_blocks3(C).n() <= (bytes == 4 ? 1100u : 640u);
+}
+
+template <typename T>
+void lc_down(const CoarseLevel& F, const CoarseLevel& C, const T* f, T* x, T* fc, double c1,
+             double c2, double c20, double omega, hipStream_t s) {
+    KTimer kt_(T_COARSE, s, lc_bytes(F, sizeof(T), 2) + C.n_unknowns * (long)sizeof(T));
+    const LcBlocks g = lc_blocks3(F);
+    const LcNextOut<T> o{C.mx, C.my, C.mz, (long)C.sx, C.sxy, fc};
+    if (F.sym)
+        klaunch(kt_, true, (k_lc_down<T, true>), dim3(g.n()), dim3(kLcThreads), F.view<T>(), g, f, x,
+                o, (T)c1, (T)c2, (T)c20, (T)omega);
+    else
+        klaunch(kt_, true, (k_lc_down<T, false>), dim3(g.n()), dim3(kLcThreads), F.view<T>(), g, f,
+                x, o, (T)c1, (T)c2, (T)c20, (T)omega);
+    HIPCHECK(hipGetLastError());
+}
+template void lc_down<double>(const CoarseLevel&, const CoarseLevel&, const double*, double*,
+                              double*, double, double, double, double, hipStream_t);
+template void lc_down<float>(const CoarseLevel&, const CoarseLevel&, const float*, float*, float*,
+                             double, double, double, double, hipStream_t);
+
+template <typename T>
+void lc_up(const CoarseLevel& F, const CoarseLevel& C, const T* vc, const T* x, const T* f, T* out,
+           double c1, double c2, double c20, double omega, hipStream_t s) {
+    KTimer kt_(T_COARSE, s, lc_bytes(F, sizeof(T), 3) + C.n_unknowns * (long)sizeof(T));
+    const LcBlocks g = lc_blocks3(F);
+    const LcNextIn<T> v{C.mx, C.my, C.mz, (long)C.sx, C.sxy, vc};
+    klaunch(kt_, true, (k_lc_up<T>), dim3(g.n()), dim3(kLcThreads), F.view<T>(), g, x, f, out, v,
+            (T)c1, (T)c2, (T)c20, (T)omega);
+    HIPCHECK(hipGetLastError());
+}
+template void lc_up<double>(const CoarseLevel&, const CoarseLevel&, const double*, const double*,
+                            const double*, double*, double, double, double, double, hipStream_t);
+template void lc_up<float>(const CoarseLevel&, const CoarseLevel&, const float*, const float*,
+                           const float*, float*, double, double, double, double, hipStream_t);
+
 // ================================================================ Galerkin product
 //
 // Column J of A_c = P^T A P with P = (I - w D^-1 A) P_tent, computed on the 9^3 patch of

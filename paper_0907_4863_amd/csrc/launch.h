@@ -285,6 +285,17 @@ template <typename T>
 void lc_prolong(const CoarseLevel& F, const CoarseLevel& C, const T* v, T* x, double omega,
                 hipStream_t s);
 
+// Strokes of a level with the degree-2 smoother: x = smoothing of f from zero and
+// fc = P^T (f - A x); out = two smoothing steps on x + P vc (out is not x).  lc_strokes: whether
+// they are the faster form on a level, in a precision of `bytes` bytes
+bool lc_strokes(const CoarseLevel& C, int degree, int bytes);
+template <typename T>
+void lc_down(const CoarseLevel& F, const CoarseLevel& C, const T* f, T* x, T* fc, double c1,
+             double c2, double c20, double omega, hipStream_t s);
+template <typename T>
+void lc_up(const CoarseLevel& F, const CoarseLevel& C, const T* vc, const T* x, const T* f, T* out,
+           double c1, double c2, double c20, double omega, hipStream_t s);
+
 // ---- setup of levels >= 1
 void rap_from_l0(const FineLevel& L, const CoarseLevel& C, double omega, hipStream_t s);
 void rap_from_lc(const CoarseLevel& F, const CoarseLevel& C, double omega, hipStream_t s);

@@ -316,12 +316,25 @@ static T* vcycle(const saamg_hierarchy* H, VBuf<T>& B, int l, const T* f0, T* ou
     }
     const LevelParams& P = H->par[l];
     const ChebCoef& c = P.cheb;
-    if (fine && l0_strokes(H->l0, c.degree, (int)sizeof(T))) {
-        T* fd = H->n_levels > 2 ? B.xb[1] : nullptr;
-        l0_down<T>(H->l0, H->lc[0], H->sym, f0, B.xa[0], B.f[1], fd, c.c1[1], c.c2[1], c.c2[0],
-                   P.omega, s);
-        T* v = vcycle<T>(H, B, 1, nullptr, nullptr, nullptr, nullptr, s);
-        l0_up<T>(H->l0, H->lc[0], v, B.xa[0], f0, out, c.c1[1], c.c2[1], c.c2[0], P.omega, dot, s);
+    const int bytes = (int)sizeof(T);
+    // a next level that runs step by step takes D^-1 f as well, in its `other` buffer (the
+    // coarsest level has none and needs none)
+    const bool steps = l + 1 < H->n_levels - 1 && !lc_strokes(H->lc[l], H->par[l + 1].cheb.degree, bytes);
+    T* fd = steps ? B.xb[l + 1] : nullptr;
+    if (fine ? l0_strokes(H->l0, c.degree, bytes) : lc_strokes(H->lc[l - 1], c.degree, bytes)) {
+        T* x = B.xa[l];
+        if (fine)
+            l0_down<T>(H->l0, H->lc[0], H->sym, f0, x, B.f[1], fd, c.c1[1], c.c2[1], c.c2[0],
+                       P.omega, s);
+        else  // the next level is smaller still: fd is null
+            lc_down<T>(H->lc[l - 1], H->lc[l], B.f[l], x, B.f[l + 1], c.c1[1], c.c2[1], c.c2[0],
+                       P.omega, s);
+        T* v = vcycle<T>(H, B, l + 1, nullptr, nullptr, nullptr, nullptr, s);
+        if (fine)
+            l0_up<T>(H->l0, H->lc[0], v, x, f0, out, c.c1[1], c.c2[1], c.c2[0], P.omega, dot, s);
+        else
+            lc_up<T>(H->lc[l - 1], H->lc[l], v, x, B.f[l], out = B.xb[l], c.c1[1], c.c2[1], c.c2[0],
+                     P.omega, s);
         return out;
     }
     const T* fl = fine ? nullptr : B.f[l];
@@ -342,9 +355,7 @@ static T* vcycle(const saamg_hierarchy* H, VBuf<T>& B, int l, const T* f0, T* ou
             std::swap(x, other);
         }
     }
-    // residual and restriction; D^-1 f of level l+1 goes to its `other` buffer (the
-    // coarsest level has none and needs none)
-    T* fd = (l + 1 < H->n_levels - 1) ? B.xb[l + 1] : nullptr;
+    // residual and restriction
     if (fine) {
         l0_residual<T, T>(H->l0, f0, x, other, s);
         l0_restrict<T>(H->l0, H->lc[0], other, B.yz, B.f[1], fd, P.omega, s);

@@ -6,7 +6,8 @@ line's stencil rows from plane to plane while the line does not change.  The cas
 lattice's edges on, one before and one after those of the tiles, and the "runs" domains change
 their cross-section along z after 1, 2, 3 and more planes, without cut walls (planes of a run
 share their rows, up to the end planes' missing neighbours) and with a different fraction at
-every wall node (no plane shares its rows).
+every wall node (no plane shares its rows).  Their coarse levels, whose strokes take tiles of 6^3
+nodes, have edges on, before and after those of the tiles as well.
 
 One V-cycle against the oracle's, element by element, max |got - want| over max |want|: fp64
 1e-11 and mixed 1e-4, the bounds of the V-cycle in test_gpu_parity (summation order, and fp32
