@@ -160,18 +160,20 @@ struct Rows {
         }
         return q;
     }
+    static __device__ __forceinline__ int slot_of(const Words& q, int b, int l) {
+        return !((q.u[l] >> b) & 1ull) ? kSlotNone
+               : !((q.r[l] >> b) & 1ull) ? kSlotRow
+                                         : q.b0[l] + (int)__popcll(q.r[l] & ((1ull << b) - 1ull));
+    }
     // returns the lanes whose column holds an unknown
     __device__ __forceinline__ uint64_t keep(const Words& q, int x, int g) {
         int* e = ring + (g % 3) * 192 + threadIdx.x;
-        const int b = x & 63;
         bool u = false;
 #pragma unroll
         for (int l = 0; l < 3; ++l) {
-            const bool un = (q.u[l] >> b) & 1ull;
-            u = u || un;
-            e[64 * l] = !un ? kSlotNone
-                        : !((q.r[l] >> b) & 1ull) ? kSlotRow
-                                                  : q.b0[l] + (int)__popcll(q.r[l] & ((1ull << b) - 1ull));
+            const int s = slot_of(q, x & 63, l);
+            u = u || s != kSlotNone;
+            e[64 * l] = s;
         }
         return __ballot(u);
     }
@@ -218,9 +220,11 @@ struct Rows {
             (void)keep(words(v, x, yb, p0, i), x, g);
         }
         const int* e = ring + (g % 3) * 192 + threadIdx.x;
-        int slot[3];
-#pragma unroll
-        for (int l = 0; l < 3; ++l) slot[l] = e[64 * l];
+        const int slot[3] = {e[0], e[64], e[128]};
+        fill(v, slot);
+    }
+    // The rows of the given slots.
+    __device__ __forceinline__ void fill(const StrokeView<T>& v, const int (&slot)[3]) {
 #pragma unroll
         for (int l = 0; l < 3; ++l) {
             c.um[l] = __ballot(slot[l] != kSlotNone);
@@ -238,6 +242,19 @@ struct Rows {
         // path waits for none of them (nor, with them, for the planes in flight)
         settle(c.a);
         if (TR) settle(c.at);
+    }
+    // For a march with a single stencil, which takes the planes in order: rows of plane i
+    // (false: the lines hold no unknown there).
+    __device__ __forceinline__ bool next(const StrokeView<T>& v, int x, int yb, int p0, int i) {
+        if (!((unk >> i) & 1ull)) return false;
+        if ((change >> i) & 1ull) {
+            const Words q = words(v, x, yb, p0, i);
+            int slot[3];
+#pragma unroll
+            for (int l = 0; l < 3; ++l) slot[l] = slot_of(q, x & 63, l);
+            fill(v, slot);
+        }
+        return true;
     }
 };
 

@@ -252,7 +252,8 @@ struct FineLevel {
     int32_t* base_full = nullptr;  // the same before de-duplication (one row per node)
     uint8_t* zinfo = nullptr;   // [ny][nz + 1]: which planes share a line's rows (stroke.hip)
     StrokeTile stroke[2][2];    // [fp32, fp64][down, up]
-    int32_t* tiles = nullptr;   // their lists of tiles
+    StrokeTile col;             // blocks of the CG passes by columns (cgcols.hip)
+    int32_t* tiles = nullptr;   // the lists of tiles
     long n_irr = 0;             // irregular rows
     long n_tab = 0;             // table rows: lines repeating the line one plane below share
                                 // its rows (see l0_dedup_table)

@@ -53,9 +53,11 @@ bool l0_wide_default(int nx) { return nx % 4 == 0 && nx > 128; }
 
 long cg_resid_parts(const FineLevel& L) { return L.wide ? l0_wblocks(L, 2) : l0_blocks(L); }
 long cg_pq_parts(const FineLevel& L, bool ring, int bytes) {
+    if (l0_cols(L)) return l0_col_parts(L);
     return ring ? l0_wblocks(L, cg_dir_lanes(bytes)) : l0_blocks(L);
 }
 long cg_xr_parts(const FineLevel& L, bool ring, int bytes) {
+    if (l0_cols(L)) return l0_col_parts(L);
     return ring ? l0_wblocks(L, cg_xr_lanes(bytes)) : l0_blocks(L);
 }
 long l0_dot_parts(const FineLevel& L, int bytes) {

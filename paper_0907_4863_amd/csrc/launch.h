@@ -161,6 +161,18 @@ void l0_up(const FineLevel& L, const CoarseLevel& C, const T* vc, const T* x, co
            double c1, double c2, double c20, double omega, double* dot, hipStream_t s);
 long l0_stroke_parts(const FineLevel& L, int bytes);
 
+// ---- level 0, the CG passes by columns (cgcols.hip), over l0_col_parts blocks
+bool l0_cols(const FineLevel& L);
+long l0_col_parts(const FineLevel& L);
+constexpr int kColX = 62, kColLines = 12;  // columns and lines of a block's tile
+// pn = z + beta p and the partials of pn . A pn; x += S_XA p
+template <typename TZ>
+void col_dir(const FineLevel& L, const TZ* z, double* x, const double* p, double* pn,
+             const double* scal, double* partials, hipStream_t s);
+// r -= S_XA A p, r32 (nullable) its fp32 copy, partials of r . r
+void col_res(const FineLevel& L, const double* p, double* r, float* r32, const double* scal,
+             double* partials, hipStream_t s);
+
 // ---- level 0 on 16-byte lanes (wide.hip; FineLevel::wide).  The launchers of fine.hip
 // dispatch to these; they take the caller's kernel timer.
 template <typename T>
@@ -237,6 +249,7 @@ void cg_resid(const FineLevel& L, const double* bs, const double* x, double* r, 
 template <typename TZ>
 void cg_pq(const FineLevel& L, const TZ* z, double* x, double* p, double* q, const double* scal,
            double* partials, hipStream_t s);
+
 template <class E>
 void cg_pdir(const FineLevel& L, const E* z, const E* p, E* pn, const double* scal,
              double* partials, hipStream_t s);

@@ -403,7 +403,7 @@ struct saamg_state {
     double *x = nullptr, *r = nullptr, *q = nullptr, *bs = nullptr;
     float* r32 = nullptr;  // fp32 copy of r (mixed precision)
     void* z = nullptr;     // preconditioned residual (fp32 in mixed precision)
-    void* p = nullptr;     // direction of the fused form (fp64)
+    double* p = nullptr;   // direction of the fused form (fp64)
     // ring form (cg_ring): the last `ringk` directions in the working precision (`pw`
     // bytes), ring slot k % ringk holding step k's; x has received alpha_j p_j for all but
     // the last `pend` of them.  q is then only the scratch of a final true residual.
@@ -480,7 +480,7 @@ static void state_alloc(saamg_state* S, saamg_hierarchy* H, bool pinned = true) 
         S->ringk = pinned ? cg_ring_len(n, S->pw, H->opt.cg_ring) : 2;
         S->ring = dmalloc((size_t)S->pw * S->ringk * n);
     } else {
-        S->p = dmalloc(8 * n);
+        S->p = (double*)dmalloc(8 * n);
     }
     S->q = (double*)dmalloc(8 * n);
     S->bs = (double*)dmalloc(8 * n);
@@ -499,6 +499,7 @@ static void state_alloc(saamg_state* S, saamg_hierarchy* H, bool pinned = true) 
     if (H->l0.wide)
         S->npart = std::max(S->npart, std::max(l0_wblocks(H->l0, 2), l0_wblocks(H->l0, 4)));
     if (strokes(H, S->pw)) S->npart = std::max(S->npart, l0_stroke_parts(H->l0, S->pw));
+    if (l0_cols(H->l0)) S->npart = std::max(S->npart, l0_col_parts(H->l0));
     S->part = (double*)dmalloc(sizeof(double) * 3 * S->npart);
     S->scal = (double*)dmalloc(sizeof(double) * S_NSLOTS);
     if (!pinned) {
@@ -523,7 +524,8 @@ static void state_release(saamg_state* S) {
     if (S->hscal && S->hscal != S->hbuf) (void)hipHostFree(S->hscal);
     if (S->ev) (void)hipEventDestroy(S->ev);
     S->x = S->r = S->q = S->bs = nullptr;
-    S->z = S->p = nullptr;
+    S->z = nullptr;
+    S->p = nullptr;
     S->ring = nullptr;
     S->part = S->scal = S->hscal = nullptr;
     S->ev = nullptr;
@@ -626,6 +628,13 @@ static void state_enqueue(saamg_state* S) {
         else
             cg_pdir<double>(L, (const double*)S->z, ring_at<double>(S, S->kdir - 1),
                             ring_at<double>(S, S->kdir), S->scal, S->part, S->s);
+    } else if (l0_cols(L)) {
+        // the new direction goes to the other buffer (the neighbours still read the old one)
+        if (S->mixed)
+            col_dir<float>(L, (const float*)S->z, S->x, (const double*)S->p, S->q, S->scal, S->part, S->s);
+        else
+            col_dir<double>(L, (const double*)S->z, S->x, (const double*)S->p, S->q, S->scal, S->part, S->s);
+        std::swap(S->p, S->q);
     } else if (S->mixed)
         cg_pq<float>(L, (const float*)S->z, S->x, (double*)S->p, S->q, S->scal, S->part, S->s);
     else
@@ -640,6 +649,8 @@ static void state_enqueue(saamg_state* S) {
                               S->s);
         S->kdir += 1;
         S->pend += 1;
+    } else if (l0_cols(L)) {
+        col_res(L, S->p, S->r, S->r32, S->scal, S->part, S->s);
     } else {
         cg_xr(L, S->r, S->q, S->scal, S->part, S->r32, S->s);
     }

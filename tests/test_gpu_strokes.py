@@ -97,3 +97,31 @@ def test_vcycle_where_the_cross_section_changes_along_z(cut, variant):
                      variant, sa.default_options(precision=precision))
         check(dom, sys_, H, G, precision, f"runs cut={cut}")
         sa.destroy(G)
+
+
+def test_solve_with_the_cg_passes_by_columns():
+    """Narrow boxes from 600 thousand unknowns on take the CG passes whose blocks cover 62 columns,
+    12 lines and 6 or 12 planes; lines of 2 * 62 + 1 nodes, 9 * 12 + 1 lines and a ragged last
+    slab.  Bounds of the solves in test_gpu_parity: fp64 1e-8 with iterations +-1, mixed 1e-6
+    against the oracle's 1e-13 solution."""
+    shape, dims = W.Shape.ellipse(1.0, 0.9, 1.5), (125, 109, 77)
+    print("[case] CG by columns, open ellipse", dims, flush=True)
+    sys_, H = solve.build(shape, *dims, W.VARIANT_QUAD, robin=True)
+    assert sys_.n >= 600000
+    b = W.rhs(W.small(shape, *dims, W.VARIANT_QUAD, robin=True))
+    o = solve.solve(sys_, H, b, tol=1e-8)
+    tight = operator.unscale(sys_, solve.solve(sys_, H, b, tol=1e-13).x)
+    want = operator.unscale(sys_, o.x)
+    bt = torch.from_numpy(b.reshape(-1)).to("cuda:0")
+    for precision in (sa.FP64, sa.MIXED):
+        G = sa.setup(sa.domain_for(shape, *dims, True), W.VARIANT_QUAD, sa.default_options(precision=precision))
+        x = torch.zeros_like(bt)
+        res = sa.solve(G, bt, x, tol=1e-8)
+        xg = x.cpu().numpy().reshape(sys_.dom.mask.shape)
+        ref, lim = (want, 1e-8) if precision == sa.FP64 else (tight, 1e-6)
+        err = np.linalg.norm(sys_.gather(xg) - ref) / np.linalg.norm(ref)
+        print(f"precision={precision} oracle it={o.iterations} gpu it={res['iterations']} err={err:.2e}", flush=True)
+        assert res["status"] == 0 and np.all(xg[~sys_.dom.mask] == 0) and err <= lim
+        if precision == sa.FP64:
+            assert abs(res["iterations"] - o.iterations) <= 1
+        sa.destroy(G)
