@@ -14,7 +14,10 @@ struct saamg_pic {
     uint8_t* mask = nullptr;        // box, nonzero = unknown
     uint32_t *key = nullptr, *key_s = nullptr;
     int32_t *idx = nullptr, *idx_s = nullptr;
-    int32_t *cstart = nullptr, *cend = nullptr;
+    uint8_t* open = nullptr;        // cell, nonzero = its field stencil is on unknowns only
+    double *run = nullptr, *carry = nullptr;  // corner sums of the runs of equal cells
+    int32_t* cell = nullptr;        // first sorted particle of each occupied cell
+    int32_t* row = nullptr;         // first sorted particle of each lattice row of cells
     void* tmp = nullptr;
     size_t tmp_bytes = 0;
 };
@@ -52,6 +55,9 @@ enum ChebMode { CHEB_ZERO1 = 0, CHEB_ZERO2, CHEB_FIRST, CHEB_NEXT, CHEB_NEXT_X }
 void pic_deposit(saamg_pic* P, const double* pos, long n, double q, double* rho, hipStream_t s);
 void pic_gather(saamg_pic* P, const double* phi, const double* pos, long n, double* E, hipStream_t s);
 size_t pic_sort_bytes(long n, int bits);
+// Bytes of the deposition's work arrays for cap particles.
+void pic_workspace(long ncell, long nrow, long cap, size_t* run, size_t* carry, size_t* row);
+void pic_open(saamg_pic* P, hipStream_t s);
 
 // Nodes per lane of the level-0 kernels on 16-byte lanes, for values of `bytes` bytes.
 constexpr int l0_lanes(int bytes) { return 16 / bytes; }

@@ -2050,11 +2050,17 @@ int saamg_pic_create(const saamg_grid* g, const uint8_t* mask, int64_t max_parti
             P->key_s = (uint32_t*)dmalloc(4 * c);
             P->idx = (int32_t*)dmalloc(4 * c);
             P->idx_s = (int32_t*)dmalloc(4 * c);
-            P->cstart = (int32_t*)dmalloc(4 * ncell);
-            P->cend = (int32_t*)dmalloc(4 * ncell);
+            size_t run, carry, row;
+            pic_workspace(ncell, (long)(g->ny - 1) * (nzl - 1), c, &run, &carry, &row);
+            P->run = (double*)dmalloc(run);
+            P->carry = (double*)dmalloc(carry);
+            P->cell = (int32_t*)dmalloc(4 * ncell);
+            P->row = (int32_t*)dmalloc(row);
+            P->open = (uint8_t*)dmalloc(ncell);
+            pic_open(P, nullptr);
             P->tmp_bytes = pic_sort_bytes(c, P->key_bits);
             P->tmp = dmalloc(std::max<size_t>(P->tmp_bytes, 16));
-            // the fills and the mask upload ran on the null stream: complete them before
+            // the mask upload and the open cells ran on the null stream: complete them before
             // any stream of the caller uses the context
             HIPCHECK(hipDeviceSynchronize());
         } catch (...) {
@@ -2094,7 +2100,8 @@ int saamg_pic_destroy(saamg_pic* P) {
         if (!P) return (int)SAAMG_OK;
         MemScope ms(MemCtx{}, nullptr);
         for (void* p : {(void*)P->mask, (void*)P->key, (void*)P->key_s, (void*)P->idx,
-                        (void*)P->idx_s, (void*)P->cstart, (void*)P->cend, P->tmp})
+                        (void*)P->idx_s, (void*)P->run, (void*)P->carry, (void*)P->cell,
+                        (void*)P->row, (void*)P->open, P->tmp})
             if (p) dfree(p);
         delete P;
         return (int)SAAMG_OK;
