@@ -316,7 +316,8 @@ void lc_up(const CoarseLevel& F, const CoarseLevel& C, const T* vc, const T* x, 
            double c1, double c2, double c20, double omega, hipStream_t s);
 
 // ---- setup of levels >= 1
-void rap_from_l0(const FineLevel& L, const CoarseLevel& C, double omega, hipStream_t s);
+void rap_from_l0(const FineLevel& L, const CoarseLevel& C, double omega, double* con, uint8_t* done,
+                 hipStream_t s);
 void rap_from_lc(const CoarseLevel& F, const CoarseLevel& C, double omega, hipStream_t s);
 void lc_finish(CoarseLevel& C, int32_t* counts, hipStream_t s);    // invD and unknown count
 void lc_to_fp32(CoarseLevel& C, hipStream_t s);

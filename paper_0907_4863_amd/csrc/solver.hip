@@ -995,8 +995,9 @@ static LevelParams level_params(saamg_hierarchy* H, int l, hipStream_t s) {
 // per-64 counts, which the caller frees.
 static int64_t galerkin(saamg_hierarchy* H, int l, CoarseLevel& C, double omega,
                         int32_t** cnt_out, hipStream_t s) {
+    Tmp con(8 * 27), done(l == 0 ? (size_t)C.mx * C.my * C.mz : 1);
     if (l == 0)
-        rap_from_l0(H->l0, C, omega, s);
+        rap_from_l0(H->l0, C, omega, con.as<double>(), done.as<uint8_t>(), s);
     else
         rap_from_lc(H->lc[l - 1], C, omega, s);
     const long nb = (C.nstore + 255) / 256;
