@@ -1249,14 +1249,27 @@ __global__ void k_lc_classify(LCView<double> c, long n, long ref, int32_t* __res
     if ((threadIdx.x & 63) == 0 && t < n) cnt[t >> 6] = __popcll(bal);
 }
 
-// Pass 3: nodes marked -3 take the slot of the node one plane below, column by column.
+// Pass 3: nodes marked -3 take the slot of the node one plane below, column by column, 16
+// planes loaded at a time (one by one, each behind the store before it: 28 us for the first
+// coarse level of a 145 x 145 x 435 ellipse).
 __global__ void k_lc_zshare(int32_t* __restrict__ slot, int sx, int sy, int sz) {
     const long t = blockIdx.x * (long)blockDim.x + threadIdx.x;
     if (t >= (long)sx * sy) return;
     const long sxy = (long)sx * sy;
-    for (int z = 1; z < sz; ++z) {
-        const long i = t + sxy * z;
-        if (slot[i] == -3) slot[i] = slot[i - sxy];
+    constexpr int U = 16;
+    int below = slot[t];
+    for (int z0 = 1; z0 < sz; z0 += U) {
+        int v[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) v[k] = slot[t + sxy * min(z0 + k, sz - 1)];
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            if (z0 + k >= sz) break;
+            if (v[k] == -3)
+                slot[t + sxy * (z0 + k)] = below;
+            else
+                below = v[k];
+        }
     }
 }
 

@@ -779,18 +779,24 @@ __global__ void __launch_bounds__(kThreads) k_l0_line_info(L0View<double> v,
 }
 
 // Slot of each line's first row: the compacted offset of the last line at or below it
-// (same y) that does not repeat.  One thread per y.
-__global__ void __launch_bounds__(256) k_l0_line_src(int ny, int nz, const int32_t* __restrict__ same,
-                                                     const int32_t* __restrict__ off,
-                                                     int32_t* __restrict__ nb) {
-    const int y = blockIdx.x * blockDim.x + threadIdx.x;
-    if (y >= ny) return;
-    int m = 0;
-#pragma unroll 8
-    for (int z = 0; z < nz; ++z) {
+// (same y) that does not repeat.  One wavefront per y, 64 planes at a time, by a scan for the
+// last plane that does not repeat (one thread per y walking up 435 planes: 113 us).
+__global__ void __launch_bounds__(64) k_l0_line_src(int ny, int nz, const int32_t* __restrict__ same,
+                                                    const int32_t* __restrict__ off,
+                                                    int32_t* __restrict__ nb) {
+    const int y = blockIdx.x, lane = threadIdx.x;
+    int carry = 0;  // plane 0 never repeats
+    for (int z0 = 0; z0 < nz; z0 += kWave) {
+        const int z = z0 + lane;
         const long line = (long)z * ny + y;
-        m = same[line] ? m : off[line];
-        nb[line] = m;
+        const bool own = z < nz && !same[line];
+        const uint64_t below = __ballot(own) & (~0ull >> (63 - lane));
+        const int o = own ? off[line] : 0;
+        const int from = below ? 63 - __clzll(below) : 0;
+        const int m = __shfl(o, from);
+        const int v = below ? m : carry;
+        if (z < nz) nb[line] = v;
+        carry = __shfl(v, kWave - 1);
     }
 }
 
@@ -835,7 +841,7 @@ void l0_dedup_table(FineLevel& L, const double* full64, const float* full32, hip
     hipLaunchKernelGGL(k_l0_line_info, gl, bl, 0, s, L.view<double>(), (const int32_t*)L.base_full,
                        full64, L.n_irr, keep.as<int32_t>(), same.as<int32_t>());
     exclusive_scan(keep.as<int32_t>(), off.as<int32_t>(), nlines, tot.as<int64_t>(), s);
-    hipLaunchKernelGGL(k_l0_line_src, dim3((unsigned)((L.ny + 255) / 256)), dim3(256), 0, s, L.ny,
+    hipLaunchKernelGGL(k_l0_line_src, dim3((unsigned)L.ny), dim3(kWave), 0, s, L.ny,
                        L.nz, (const int32_t*)same.as<int32_t>(), (const int32_t*)off.as<int32_t>(),
                        nb.as<int32_t>());
     hipLaunchKernelGGL(k_l0_seg_base, dim3((unsigned)((L.nseg + 255) / 256)), dim3(256), 0, s,
