@@ -107,6 +107,12 @@ void zero_fill(void* p, size_t bytes, hipStream_t s);
 
 // ---- level 0: build
 void l0_scatter_nwidx(int32_t* nwidx, const int64_t* nodes, long n, hipStream_t s);
+// Near-wall rows of the wall entries and open-end planes: nwidx (-1 before) receives the row of
+// each such node, frac (6 per row, n_wall rows and 2 nx ny more with open ends) its wall
+// fractions; *bad (0 before) is set when the domain needs prepare_domain.
+void l0_wall_rows(int nx, int ny, int nz, const uint8_t* mask, bool scan_mask, bool open, const int64_t* node,
+                  const uint8_t* dir, const double* sv, long n_wall, bool cuts, int32_t* nwidx, double* frac,
+                  int* bad, hipStream_t s);
 void l0_build_masks(FineLevel& L, const uint8_t* mask, const int32_t* nwidx, int32_t* cnt_irr,
                     int32_t* cnt_unk, hipStream_t s);
 // true when the segment masks unk/irr equal L's

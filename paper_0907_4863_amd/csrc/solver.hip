@@ -920,33 +920,83 @@ static void validate_options(const saamg_options& o) {
         throw ApiError{SAAMG_INVALID_ARG, "l0_wide must be 0, 1 or 2"};
 }
 
+// Whether the device's checks can take the domain: its scalars are in range (prepare_domain
+// names what is not) and, where the mask is scanned, it has an unknown.
+static bool device_checks(const saamg_domain* dom, int variant, bool scan_mask) {
+    if (!dom || !dom->mask || dom->nx < 3 || dom->ny < 3 || dom->nz < 3) return false;
+    const double nbox = (double)dom->nx * dom->ny * dom->nz;
+    if (nbox > 2.0e9 || !(dom->hx > 0) || !(dom->hy > 0) || !(dom->hz > 0)) return false;
+    if (variant < SAAMG_VARIANT_CONST || variant > SAAMG_VARIANT_QUAD) return false;
+    if (!(dom->robin_d >= 0.0) || !std::isfinite(dom->robin_d)) return false;
+    if (dom->robin_d > 0.0 && dom->nz < 4) return false;
+    if (dom->n_wall < 0 || dom->n_wall > 1000000000L) return false;
+    if (dom->n_wall > 0 && (!dom->wall_node || !dom->wall_dir || !dom->wall_s)) return false;
+    if (!scan_mask) return true;
+    const uint8_t* m = dom->mask;
+    const uint8_t* end = m + (long)dom->nx * dom->ny * dom->nz;
+    return std::find_if(m, end, [](uint8_t c) { return c != 0; }) != end;
+}
+
+
 struct DeviceDomain {
     uint8_t* mask = nullptr;
     int32_t* nwidx = nullptr;
     int64_t* nwnodes = nullptr;
     double* nwfrac = nullptr;
-    DeviceDomain(const saamg_domain* dom, const DomainPrep& D, long nbox, hipStream_t s) {
+    // `prep`: the domain's rows when the host has prepared them (a domain that the device's
+    // checks cannot take); otherwise the device checks the domain and forms its rows, and
+    // prepare_domain has the last word on one that they do not pass
+    DeviceDomain(const saamg_domain* dom, int variant, bool scan_mask, const DomainPrep* prep, long nbox,
+                 hipStream_t s) {
         try {
             mask = (uint8_t*)dmalloc(nbox);
             nwidx = (int32_t*)dmalloc(4 * nbox);
-            nwnodes = (int64_t*)dmalloc(8 * std::max<size_t>(D.nw_nodes.size(), 1));
-            nwfrac = (double*)dmalloc(8 * std::max<size_t>(D.nw_frac.size(), 1));
-            // uploads and the fill are queued on s, ordered before the kernels that read
-            // them; the host arrays outlive the setup's next synchronisation of s
+            // uploads and fills are queued on s, ordered before the kernels that read them; the
+            // host arrays outlive the setup's next synchronisation of s
             HIPCHECK(hipMemcpyAsync(mask, dom->mask, nbox, hipMemcpyHostToDevice, s));
             HIPCHECK(hipMemsetAsync(nwidx, 0xff, 4 * nbox, s));
-            if (!D.nw_nodes.empty()) {
-                HIPCHECK(hipMemcpyAsync(nwnodes, D.nw_nodes.data(), 8 * D.nw_nodes.size(),
-                                        hipMemcpyHostToDevice, s));
-                HIPCHECK(hipMemcpyAsync(nwfrac, D.nw_frac.data(), 8 * D.nw_frac.size(),
-                                        hipMemcpyHostToDevice, s));
+            if (prep) {
+                upload(*prep, s);
+            } else if (!form(dom, variant, scan_mask, s)) {
+                const DomainPrep D = prepare_domain(dom, variant, scan_mask);
+                HIPCHECK(hipMemsetAsync(nwidx, 0xff, 4 * nbox, s));
+                dfree(nwfrac);
+                nwfrac = nullptr;
+                upload(D, s);
             }
-            l0_scatter_nwidx(nwidx, nwnodes, (long)D.nw_nodes.size(), s);
-            HIPCHECK(hipStreamSynchronize(s));
         } catch (...) {
             release();
             throw;
         }
+    }
+    void upload(const DomainPrep& D, hipStream_t s) {
+        nwnodes = (int64_t*)dmalloc(8 * std::max<size_t>(D.nw_nodes.size(), 1));
+        nwfrac = (double*)dmalloc(8 * std::max<size_t>(D.nw_frac.size(), 1));
+        if (!D.nw_nodes.empty()) {
+            HIPCHECK(hipMemcpyAsync(nwnodes, D.nw_nodes.data(), 8 * D.nw_nodes.size(),
+                                    hipMemcpyHostToDevice, s));
+            HIPCHECK(hipMemcpyAsync(nwfrac, D.nw_frac.data(), 8 * D.nw_frac.size(),
+                                    hipMemcpyHostToDevice, s));
+        }
+        l0_scatter_nwidx(nwidx, nwnodes, (long)D.nw_nodes.size(), s);
+        HIPCHECK(hipStreamSynchronize(s));
+    }
+    bool form(const saamg_domain* dom, int variant, bool scan_mask, hipStream_t s) {
+        const long nxy = (long)dom->nx * dom->ny, n = dom->n_wall;
+        const bool open = dom->robin_d > 0.0, cuts = variant != SAAMG_VARIANT_CONST;
+        Tmp node(8 * n), dir(n), sv(8 * n), bad(4);
+        nwfrac = (double*)dmalloc(48 * (n + (open ? 2 * nxy : 0)));
+        if (n > 0) {
+            HIPCHECK(hipMemcpyAsync(node.p, dom->wall_node, 8 * n, hipMemcpyHostToDevice, s));
+            HIPCHECK(hipMemcpyAsync(dir.p, dom->wall_dir, n, hipMemcpyHostToDevice, s));
+            HIPCHECK(hipMemcpyAsync(sv.p, dom->wall_s, 8 * n, hipMemcpyHostToDevice, s));
+        }
+        l0_wall_rows(dom->nx, dom->ny, dom->nz, mask, scan_mask, open, node.as<int64_t>(),
+                     dir.as<uint8_t>(), sv.as<double>(), n, cuts, nwidx, nwfrac, bad.as<int>(), s);
+        int b = 0;
+        HIPCHECK(hipMemcpyAsync(&b, bad.p, 4, hipMemcpyDeviceToHost, s));
+        HIPCHECK(hipStreamSynchronize(s));
+        return b == 0;
     }
     void release() {
         for (void* p : {(void*)mask, (void*)nwidx, (void*)nwnodes, (void*)nwfrac}) dfree(p);
@@ -1073,17 +1123,25 @@ static void coarse_fp32(saamg_hierarchy* H, hipStream_t s) {
 static saamg_hierarchy* setup_impl(const saamg_domain* dom, int variant, const saamg_options* opt,
                                    hipStream_t s) {
     auto t0 = std::chrono::steady_clock::now();
-    const DomainPrep D = prepare_domain(dom, variant);
+    const bool on_device = device_checks(dom, variant, true);
+    DomainPrep D;
+    if (!on_device) D = prepare_domain(dom, variant);
     const double t_host = ms_since(t0);
     saamg_options o;
     if (opt)
         o = *opt;
     else
         saamg_default_options(&o);
-    validate_options(o);
+    try {
+        validate_options(o);
+    } catch (...) {
+        if (on_device) prepare_domain(dom, variant);  // an error of the domain comes first
+        throw;
+    }
     const int nx = dom->nx, ny = dom->ny, nz = dom->nz;
     const long nxy = (long)nx * ny, nbox = nxy * nz;
 
+    bool checked = !on_device;
     saamg_hierarchy* H = new saamg_hierarchy();
     H->mem.alloc = o.alloc;
     H->mem.free = o.free;
@@ -1093,6 +1151,8 @@ static saamg_hierarchy* setup_impl(const saamg_domain* dom, int variant, const s
         H->variant = variant;
         H->opt = o;
         H->sym = variant != SAAMG_VARIANT_QUAD;
+        DeviceDomain dd(dom, variant, true, on_device ? nullptr : &D, nbox, s);
+        checked = true;
         FineLevel& L = H->l0;
         L.nx = nx;
         L.ny = ny;
@@ -1117,7 +1177,6 @@ static saamg_hierarchy* setup_impl(const saamg_domain* dom, int variant, const s
         L.sigma = (double*)dmalloc(8 * nbox);
 
         // segment masks of unknowns and irregular rows, table slots
-        DeviceDomain dd(dom, D, nbox, s);
         int64_t tots[2];
         {
             // two totals: the second scan's total sits in the first one's scratch, which it
@@ -1217,6 +1276,7 @@ static saamg_hierarchy* setup_impl(const saamg_domain* dom, int variant, const s
         H->t_phase_ms[5] = ms_since(tc);
     } catch (...) {
         saamg_destroy(H);
+        if (!checked) prepare_domain(dom, variant);  // an error of the domain comes first
         throw;
     }
     H->t_setup_ms = ms_since(t0);
@@ -1225,16 +1285,19 @@ static saamg_hierarchy* setup_impl(const saamg_domain* dom, int variant, const s
 
 // Checks shared by the re-setups of H for a new domain: the box, the end condition kind
 // and no live solve state.
-static DomainPrep check_resetup(const saamg_hierarchy* H, const saamg_domain* dom) {
+// Returns the domain's rows as DeviceDomain takes them (`prep` null: formed on the device).
+static const DomainPrep* check_resetup(const saamg_hierarchy* H, const saamg_domain* dom, DomainPrep& D) {
     const FineLevel& L = H->l0;
     if (dom && dom->mask && (dom->nx != L.nx || dom->ny != L.ny || dom->nz != L.nz))
         throw ApiError{SAAMG_INVALID_ARG, "the domain's box differs from the hierarchy's"};
-    DomainPrep D = prepare_domain(dom, H->variant, false);
+    const bool on_device = device_checks(dom, H->variant, false);
+    const bool other_ends = on_device && (dom->robin_d > 0.0) != (L.robin_d > 0.0);
+    if (!on_device || other_ends || H->live_states > 0) D = prepare_domain(dom, H->variant, false);
     if ((dom->robin_d > 0.0) != (L.robin_d > 0.0))
         throw ApiError{SAAMG_INVALID_ARG, "the end condition kind (open or closed) differs"};
     if (H->live_states > 0)
         throw ApiError{SAAMG_INVALID_ARG, "solve states of this hierarchy still exist"};
-    return D;
+    return on_device ? nullptr : &D;
 }
 
 // The new domain's segment masks (unknowns and near-wall rows) must equal H's.
@@ -1268,8 +1331,9 @@ static void drop_operator(saamg_hierarchy* H) {
 static void refresh_impl(saamg_hierarchy* H, const saamg_domain* dom, hipStream_t s) {
     auto t0 = std::chrono::steady_clock::now();
     FineLevel& L = H->l0;
-    const DomainPrep D = check_resetup(H, dom);
-    DeviceDomain dd(dom, D, L.nbox, s);
+    DomainPrep D;
+    const DomainPrep* prep = check_resetup(H, dom, D);
+    DeviceDomain dd(dom, H->variant, false, prep, L.nbox, s);
     check_same_rows(H, dd, s);
     // from here on H changes; a failure leaves it unusable (destroy it)
     drop_operator(H);
@@ -1296,8 +1360,9 @@ static void refresh_impl(saamg_hierarchy* H, const saamg_domain* dom, hipStream_
 // (stencil weights, wall rows, scaling) of dom; the V-cycle keeps everything it had.
 static void set_operator_impl(saamg_hierarchy* H, const saamg_domain* dom, hipStream_t s) {
     const FineLevel& L = H->l0;
-    const DomainPrep D = check_resetup(H, dom);
-    DeviceDomain dd(dom, D, L.nbox, s);
+    DomainPrep D;
+    const DomainPrep* prep = check_resetup(H, dom, D);
+    DeviceDomain dd(dom, H->variant, false, prep, L.nbox, s);
     check_same_rows(H, dd, s);
     if (!H->op) {
         // shares the segment masks and the rows' full slots; its own de-duplicated slots

@@ -1,0 +1,85 @@
+"""The setup's domain checks and near-wall rows on the device: the hierarchy of a domain whose wall
+entries are in any other order (which the host sorts) is the same bit for bit, and an invalid
+domain is refused with the host's message."""
+import numpy as np
+import pytest
+
+import workloads as W
+
+torch = pytest.importorskip("torch")
+sa = pytest.importorskip("paper_0907_4863_amd")
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = {"cyl": W.Shape.cylinder(1.0, 2.0), "ell": W.Shape.ellipse(1.0, 0.6, 4.0),
+          "box": W.Shape.boxbore(0.8, 4.0)}
+
+
+def _copy(d, **kw):
+    a = dict(mask=d.mask.copy(), h=d.h, wall_node=d.wall_node.copy(), wall_dir=d.wall_dir.copy(),
+             wall_s=d.wall_s.copy(), robin_d=d.robin_d)
+    a.update(kw)
+    return sa.HostDomain(**a)
+
+
+def _everything(dom, variant):
+    G = sa.setup(dom, variant, sa.default_options())
+    info = sa.hierarchy_info(G)
+    out = [sa.level_coefficients(G, l, info["dims"][l]) for l in range(info["n_levels"])]
+    sig = torch.zeros(dom.mask.size, dtype=torch.float64, device="cuda:0")
+    sa.scaling(G, sig)
+    sa.destroy(G)
+    return out + [sig.cpu().numpy()]
+
+
+@pytest.mark.parametrize("variant", [W.VARIANT_CONST, W.VARIANT_LIN, W.VARIANT_QUAD])
+@pytest.mark.parametrize("shape,open_ends", [("cyl", False), ("ell", True), ("box", False)])
+def test_rows_formed_on_the_device_are_the_hosts(shape, open_ends, variant):
+    print(f"[case] domain rows {shape} open={open_ends} variant={variant}", flush=True)
+    dom = sa.domain_for(SHAPES[shape], 31, 27, 36, open_ends=open_ends)
+    order = np.random.default_rng(5).permutation(dom.wall_node.size)
+    mixed = _copy(dom, wall_node=dom.wall_node[order], wall_dir=dom.wall_dir[order],
+                  wall_s=dom.wall_s[order])
+    for got, want in zip(_everything(dom, variant), _everything(mixed, variant)):
+        assert np.array_equal(got, want)
+
+
+def _face(d):
+    d.mask[d.nz // 2, d.ny // 2, 0] = 1
+    return d
+
+
+def _end(d):
+    d.mask[2, d.ny // 2, d.nx // 2] = 0
+    return d
+
+
+def _repeat(d):
+    k = d.wall_node.size // 2
+    ins = lambda a: np.insert(a, k, a[k])
+    return _copy(d, wall_node=ins(d.wall_node), wall_dir=ins(d.wall_dir), wall_s=ins(d.wall_s))
+
+
+def _set(name, value):
+    def f(d):
+        getattr(d, name)[d.wall_node.size - 1] = value
+        return d
+    return f
+
+
+@pytest.mark.parametrize("spoil,open_ends,message", [
+    (_face, False, "face of the box"),
+    (_end, True, "open-end unknown"),
+    (_repeat, False, "duplicate wall entry"),
+    (_set("wall_s", 0.0), False, "wall fraction"),
+    (_set("wall_s", np.nan), True, "wall fraction"),
+    (_set("wall_dir", 6), False, "out of range"),
+    (_set("wall_node", -1), False, "out of range"),
+    (_set("wall_node", 10 ** 12), True, "out of range"),
+    (_set("wall_node", 0), False, "must name an unknown"),
+], ids=lambda v: v if isinstance(v, str) else None)
+def test_invalid_domains_are_refused(spoil, open_ends, message):
+    print(f"[case] invalid domain: {message} open={open_ends}", flush=True)
+    dom = spoil(_copy(sa.domain_for(SHAPES["cyl"], 21, 21, 24, open_ends=open_ends)))
+    with pytest.raises(sa.SaamgError, match=message):
+        sa.setup(dom, W.VARIANT_QUAD, sa.default_options())
