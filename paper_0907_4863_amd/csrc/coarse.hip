@@ -1150,11 +1150,22 @@ static CoefOut coef_out(const CoarseLevel& C) {
 // 435 ellipse: 1295 -> 500 us in the three launches, 128 x 128 x 256 with quadratic rows 600 -> 265.  (On the coarse levels,
 // where half the patches or fewer are interior, marking cost what it saved.)  con: 27
 // doubles; done: one byte per aggregate.
+//
+// From 32768 aggregates on: the column and the marks are two launches and two buffers more,
+// which at 64 x 64 x 128 (20,812 aggregates) cost what they save.
+bool rap_marks(const CoarseLevel& C) { return (long)C.mx * C.my * C.mz >= 32768; }
 void rap_from_l0(const FineLevel& L, const CoarseLevel& C, double omega, double* con, uint8_t* done,
                  hipStream_t s) {
     AccL0 acc{L.view<double>(), true};
     const long n = (long)C.mx * C.my * C.mz;
     const CoefOut out = coef_out(C);
+    if (!rap_marks(C)) {
+        acc.open = false;
+        hipLaunchKernelGGL((k_rap<AccL0>), dim3((unsigned)n), dim3(256), 0, s, acc, C.view<double>(), out,
+                           omega, (const uint8_t*)nullptr, (double*)nullptr);
+        HIPCHECK(hipGetLastError());
+        return;
+    }
     hipLaunchKernelGGL((k_rap<AccL0>), dim3(1), dim3(256), 0, s, acc, C.view<double>(), out, omega,
                        (const uint8_t*)nullptr, con);
     hipLaunchKernelGGL(k_rap_mark, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, acc.v,

@@ -920,8 +920,10 @@ static void validate_options(const saamg_options& o) {
         throw ApiError{SAAMG_INVALID_ARG, "l0_wide must be 0, 1 or 2"};
 }
 
-// Whether the device's checks can take the domain: its scalars are in range (prepare_domain
-// names what is not) and, where the mask is scanned, it has an unknown.
+// Whether the device checks the domain: its scalars are in range (prepare_domain names what is
+// not) and, where the mask is scanned, it has an unknown; and it has enough wall entries for
+// the uploads and launches to pay (3,720 at 33^3: 30 us on the host, 90 on the device; 31,248
+// at 64 x 64 x 128: 200 and 20).
 static bool device_checks(const saamg_domain* dom, int variant, bool scan_mask) {
     if (!dom || !dom->mask || dom->nx < 3 || dom->ny < 3 || dom->nz < 3) return false;
     const double nbox = (double)dom->nx * dom->ny * dom->nz;
@@ -929,8 +931,8 @@ static bool device_checks(const saamg_domain* dom, int variant, bool scan_mask) 
     if (variant < SAAMG_VARIANT_CONST || variant > SAAMG_VARIANT_QUAD) return false;
     if (!(dom->robin_d >= 0.0) || !std::isfinite(dom->robin_d)) return false;
     if (dom->robin_d > 0.0 && dom->nz < 4) return false;
-    if (dom->n_wall < 0 || dom->n_wall > 1000000000L) return false;
-    if (dom->n_wall > 0 && (!dom->wall_node || !dom->wall_dir || !dom->wall_s)) return false;
+    if (dom->n_wall < 16384 || dom->n_wall > 1000000000L) return false;
+    if (!dom->wall_node || !dom->wall_dir || !dom->wall_s) return false;
     if (!scan_mask) return true;
     const uint8_t* m = dom->mask;
     const uint8_t* end = m + (long)dom->nx * dom->ny * dom->nz;
@@ -1045,10 +1047,15 @@ static LevelParams level_params(saamg_hierarchy* H, int l, hipStream_t s) {
 // per-64 counts, which the caller frees.
 static int64_t galerkin(saamg_hierarchy* H, int l, CoarseLevel& C, double omega,
                         int32_t** cnt_out, hipStream_t s) {
-    Tmp con(8 * 27), done(l == 0 ? (size_t)C.mx * C.my * C.mz : 1);
-    if (l == 0)
-        rap_from_l0(H->l0, C, omega, con.as<double>(), done.as<uint8_t>(), s);
-    else
+    std::unique_ptr<Tmp> con, done;
+    if (l == 0) {
+        if (rap_marks(C)) {
+            con.reset(new Tmp(8 * 27));
+            done.reset(new Tmp((size_t)C.mx * C.my * C.mz));
+        }
+        rap_from_l0(H->l0, C, omega, con ? con->as<double>() : nullptr,
+                    done ? done->as<uint8_t>() : nullptr, s);
+    } else
         rap_from_lc(H->lc[l - 1], C, omega, s);
     const long nb = (C.nstore + 255) / 256;
     int32_t* cnt = (int32_t*)dmalloc(4 * 4 * nb);

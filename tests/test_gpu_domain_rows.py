@@ -36,7 +36,8 @@ def _everything(dom, variant):
 @pytest.mark.parametrize("shape,open_ends", [("cyl", False), ("ell", True), ("box", False)])
 def test_rows_formed_on_the_device_are_the_hosts(shape, open_ends, variant):
     print(f"[case] domain rows {shape} open={open_ends} variant={variant}", flush=True)
-    dom = sa.domain_for(SHAPES[shape], 31, 27, 36, open_ends=open_ends)
+    dom = sa.domain_for(SHAPES[shape], 61, 49, 161, open_ends=open_ends)
+    assert dom.wall_node.size >= 16384  # fewer are prepared on the host
     order = np.random.default_rng(5).permutation(dom.wall_node.size)
     mixed = _copy(dom, wall_node=dom.wall_node[order], wall_dir=dom.wall_dir[order],
                   wall_s=dom.wall_s[order])
@@ -80,6 +81,7 @@ def _set(name, value):
 ], ids=lambda v: v if isinstance(v, str) else None)
 def test_invalid_domains_are_refused(spoil, open_ends, message):
     print(f"[case] invalid domain: {message} open={open_ends}", flush=True)
-    dom = spoil(_copy(sa.domain_for(SHAPES["cyl"], 21, 21, 24, open_ends=open_ends)))
+    dom = spoil(_copy(sa.domain_for(SHAPES["cyl"], 51, 51, 114, open_ends=open_ends)))
+    assert dom.wall_node.size >= 16384
     with pytest.raises(sa.SaamgError, match=message):
         sa.setup(dom, W.VARIANT_QUAD, sa.default_options())

@@ -1,8 +1,8 @@
 """GPU parity of the Galerkin product of level 0 where most aggregates have only interior rows
-around them and take one column formed for all: patches of 9 nodes that end on, before and
-after the 64-node words of the masks, boxes with one interior aggregate and with none, both
-storages (symmetric and full), open ends.  Every coefficient of every coarse level against the
-oracle's, max |got - want| over max |want| 1e-12, the bound of test_gpu_parity."""
+around them and take one column formed for all: patches of 9 nodes that straddle
+the 64-node words of the masks, both storages (symmetric and full), open ends.  Every coefficient of every coarse level against the
+oracle's, max |got - want| over max |want| 1e-12, the bound of test_gpu_parity.  The boxes of
+33,748 and 33,120 aggregates take the shared column, the small one (fewer than 32,768) does not."""
 import numpy as np
 import pytest
 
@@ -29,11 +29,9 @@ def _coef(lv):
 
 
 @pytest.mark.parametrize("shape,nx,ny,nz,variant,open_ends", [
-    (CYL, 12, 12, 12, W.VARIANT_LIN, False),
-    (CYL, 22, 22, 13, W.VARIANT_CONST, False),
-    (ELL, 75, 40, 22, W.VARIANT_LIN, False),
-    (ELL, 76, 41, 21, W.VARIANT_QUAD, True),
-    (CYL, 134, 30, 16, W.VARIANT_QUAD, False),
+    (CYL, 75, 40, 22, W.VARIANT_LIN, False),
+    (ELL, 76, 31, 353, W.VARIANT_LIN, False),
+    (CYL, 134, 24, 274, W.VARIANT_QUAD, True),
 ])
 def test_coarse_operators_with_interior_aggregates(shape, nx, ny, nz, variant, open_ends):
     print(f"[case] galerkin {shape.name} {nx}x{ny}x{nz} variant {variant}", flush=True)
