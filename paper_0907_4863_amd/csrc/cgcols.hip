@@ -1,4 +1,5 @@
-// Level-0 passes with one stencil, by columns (cols.h): the two passes of a CG step.
+// Level-0 passes with one stencil, by columns (cols.h): the two passes of a CG step, and the
+// step of the Lanczos estimate.
 //
 // A wavefront marches 3 lines of 62 columns (lanes 0 and 63 are the halo) along z and loads
 // the lines before and after them itself, so that wavefronts share nothing and no plane takes a
@@ -31,7 +32,7 @@ struct ColAt {
 // March of a wavefront: for every plane the op loads (op.load), forms its 5 values
 // (op.form(line)) and writes what needs no stencil (op.emit), then op.body(l, c, ax) takes the
 // centre and A X of the own lines.
-template <class Op>
+template <bool SP = false, class Op>
 __device__ __forceinline__ void col_march(const StrokeView<double>& v, Op& op) {
     int tx, ty, sz;
     stroke_tile(v, &tx, &ty, &sz);
@@ -53,7 +54,7 @@ __device__ __forceinline__ void col_march(const StrokeView<double>& v, Op& op) {
             at.s8[k - 1] = own ? 8u * o : kOff;
         }
     }
-    Rows<double, false> rows;
+    Rows<double, false, SP> rows;
     rows.init(v, yb, zs);
     op.start(v.nxy, zs - 1);
     op.load(at, zs >= 1);
@@ -231,6 +232,83 @@ __global__ void __launch_bounds__(kColThreads) k_col_res(StrokeView<double> v,
     if (threadIdx.x == 0 && threadIdx.y == 0) part[blockIdx.x] = s;
 }
 
+// A step of the Lanczos recurrence in one pass: y' = cu u - cc y - cp w, with u = S y and w
+// the vector before y, and u' = S y' for the next step; partials of y' . S y' and y' . y'.
+// S is the symmetric part of A (SP: A itself is not symmetric), the vectors are kept as they
+// come, and the scalars carry the norms (FIN_LZ).
+struct LzOp {
+    const double *u, *y, *w;
+    double *yn, *un;
+    int b8;
+    double cu, cc, cp;
+    double ya = 0.0, yy = 0.0;
+    double ru[5], ry[5], rw[5], val[5];
+    long nxy;
+    __device__ __forceinline__ void start(long nxy_, int zp) {
+        nxy = nxy_;
+        u += nxy * zp;
+        y += nxy * zp;
+        w += nxy * zp;
+        yn += nxy * zp;
+        un += nxy * (zp - 1);
+    }
+    __device__ __forceinline__ void load(const ColAt& at, bool ok) {
+        const auto bu = plane(u, b8, ok), by = plane(y, b8, ok), bw = plane(w, b8, ok);
+#pragma unroll
+        for (int l = 0; l < 5; ++l) {
+            bload(bu, at.l8[l], ru[l]);
+            bload(by, at.l8[l], ry[l]);
+            bload(bw, at.l8[l], rw[l]);
+        }
+        u += nxy;
+        y += nxy;
+        w += nxy;
+    }
+    __device__ __forceinline__ double form(int l) {
+        return val[l] = __builtin_fma(-cp, here(rw[l]), __builtin_fma(-cc, here(ry[l]), cu * here(ru[l])));
+    }
+    __device__ __forceinline__ void emit(const ColAt& at, bool ok) {
+        const auto b = plane((const double*)yn, b8, ok);
+#pragma unroll
+        for (int l = 0; l < 3; ++l) bstore(b, at.s8[l], val[l + 1]);
+        yn += nxy;
+    }
+    __device__ __forceinline__ void body(const ColAt& at, int l, double c, double ax) {
+        bstore(plane((const double*)un, b8, true), at.s8[l], ax);
+        const bool own = at.s8[l] != kOff;
+        ya += own ? c * ax : 0.0;
+        yy += own ? c * c : 0.0;
+    }
+    __device__ __forceinline__ void next() { un += nxy; }
+};
+
+// Bound by its 40 bytes a node.  With u = S v in a pass of its own and the update and its norm in
+// another it was 48 bytes, in marches that read masks and slots per plane (see l0_lz_cols).
+template <bool SP>
+__global__ void __launch_bounds__(kColThreads) k_col_lz(StrokeView<double> v, const double* __restrict__ u,
+                                                        const double* __restrict__ y,
+                                                        const double* __restrict__ w,
+                                                        double* __restrict__ yn, double* __restrict__ un,
+                                                        const double* __restrict__ scal, double* part) {
+    __shared__ double lds[kColThreads / kWave];
+    LzOp op;
+    op.u = u;
+    op.y = y;
+    op.w = w;
+    op.yn = yn;
+    op.un = un;
+    op.b8 = (int)(8 * v.nxy);
+    op.cu = scal[S_LZ_S];
+    op.cc = scal[S_ALPHA];
+    op.cp = scal[S_LZ_B];
+    col_march<SP>(v, op);
+    const double s0 = block_sum(op.ya, lds), s1 = block_sum(op.yy, lds);
+    if (threadIdx.x == 0 && threadIdx.y == 0) {
+        part[blockIdx.x] = s0;
+        part[gridDim.x + blockIdx.x] = s1;
+    }
+}
+
 // Whether the CG passes of a box on one-node lanes run by columns: from 600 thousand unknowns on
 // (the wavefront's start, from its tile to its rows, is four dependent loads), and where a
 // plane is within a 32-bit byte offset.  The two passes against the fused q-recursion and its
@@ -256,6 +334,21 @@ static StrokeView<double> col_view(const FineLevel& L) {
     v.S = L.col.S;
     v.skip = nullptr;
     return v;
+}
+
+// Boxes on one-node lanes, where a plane is within a 32-bit byte offset: 145 x 145 x 435 ellipse
+// 126 -> 103 us a step, 128 x 128 x 256 with quadratic rows 70 -> 44; 64 x 64 x 128 18 -> 15.  Boxes on
+// 16-byte lanes keep their two passes (256 x 256 x 768: 15 steps 8.2 ms against 8.7 by columns).
+bool l0_lz_cols(const FineLevel& L) { return !L.wide && L.nxy * 8 < (long)kOff; }
+
+void col_lz(const FineLevel& L, bool sym, const double* u, const double* y, const double* w, double* yn,
+            double* un, const double* scal, double* partials, hipStream_t s) {
+    const dim3 g((unsigned)L.col.blocks()), b(kWave, 4);
+    if (sym)
+        hipLaunchKernelGGL(k_col_lz<false>, g, b, 0, s, col_view(L), u, y, w, yn, un, scal, partials);
+    else
+        hipLaunchKernelGGL(k_col_lz<true>, g, b, 0, s, col_view(L), u, y, w, yn, un, scal, partials);
+    HIPCHECK(hipGetLastError());
 }
 
 template <typename TZ>

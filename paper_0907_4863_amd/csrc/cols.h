@@ -89,7 +89,8 @@ __device__ __forceinline__ void bstore(__amdgpu_buffer_rsrc_t r, unsigned o, dou
 }
 
 // The rows in use along a slab.  Planes are counted from the slab's first, p0; up to 64.
-template <typename T, bool TR>
+// SP: the rows of the symmetric part, (A + A^T) / 2, in place of A's.
+template <typename T, bool TR, bool SP = false>
 struct Rows {
     Cols<T, TR> c;
     uint64_t change;  // planes whose rows differ from those of the plane below; bit 0 set
@@ -236,6 +237,12 @@ struct Rows {
             if (slot[l] >= 0) {
                 load_row6(v.tab, (long)slot[l], 0u, c.a[l]);
                 if (TR) load_row6(v.tabT, (long)slot[l], 0u, c.at[l]);
+                if (SP) {
+                    T t[6];
+                    load_row6(v.tabT, (long)slot[l], 0u, t);
+#pragma unroll
+                    for (int d = 0; d < 6; ++d) c.a[l][d] = T(0.5) * (c.a[l][d] + t[d]);
+                }
             }
         }
         // the rows have landed before the branch around this read ends, so that the common

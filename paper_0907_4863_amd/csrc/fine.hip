@@ -372,6 +372,18 @@ __global__ void __launch_bounds__(kFinThreads) k_finalize(const double* __restri
             scal[S_LZ_B] = b;
             break;
         }
+        case FIN_LZ: {
+            // a step of the one-pass Lanczos recurrence (k_col_lz): sums y.Sy and y.y; alpha of
+            // y / ||y|| to scal[dst], ||y|| behind it, and the factors of the next step
+            const double b = sqrt(sums[1]), s = b > 0.0 ? 1.0 / b : 0.0;
+            const double a = sums[1] > 0.0 ? sums[0] / sums[1] : 0.0;
+            scal[dst] = a;
+            scal[dst + 1] = b;
+            scal[S_ALPHA] = a * s;
+            scal[S_LZ_B] = b * scal[S_LZ_SP];
+            scal[S_LZ_SP] = scal[S_LZ_S] = s;
+            break;
+        }
         case FIN_NORM:  // first Lanczos vector = start / ||start||_D
             scal[S_LZ_S] = 1.0 / sqrt(sums[0]);
             scal[S_LZ_SP] = 0.0;

@@ -46,7 +46,7 @@ struct RingSlots {
     int slot[kCgRing];
 };
 // Finalisation ops: how the summed partials update `scal`.
-enum FinOp { FIN_STORE = 0, FIN_ALPHA, FIN_RHO_INIT, FIN_RHO, FIN_LZ_ALPHA, FIN_LZ_BETA, FIN_NORM,
+enum FinOp { FIN_STORE = 0, FIN_ALPHA, FIN_RHO_INIT, FIN_RHO, FIN_LZ_ALPHA, FIN_LZ_BETA, FIN_LZ, FIN_NORM,
              FIN_RESTORE_RHO, FIN_XA_CLEAR, FIN_RR };
 // Chebyshev step kinds.  CHEB_NEXT_X (level 0 only) is CHEB_NEXT with the previous
 // iterate in place of the previous direction (d = xin - din).
@@ -174,6 +174,11 @@ void l0_up(const FineLevel& L, const CoarseLevel& C, const T* vc, const T* x, co
 long l0_stroke_parts(const FineLevel& L, int bytes);
 
 // ---- level 0, the CG passes by columns (cgcols.hip), over l0_col_parts blocks
+// One pass per Lanczos step on level 0 (cgcols.hip), for boxes whose planes a 32-bit byte offset
+// reaches.
+bool l0_lz_cols(const FineLevel& L);
+void col_lz(const FineLevel& L, bool sym, const double* u, const double* y, const double* w, double* yn,
+            double* un, const double* scal, double* partials, hipStream_t s);
 bool l0_cols(const FineLevel& L);
 long l0_col_parts(const FineLevel& L);
 constexpr int kColX = 62, kColLines = 12;  // columns and lines of a block's tile
@@ -322,12 +327,12 @@ void lc_up(const CoarseLevel& F, const CoarseLevel& C, const T* vc, const T* x, 
            double c1, double c2, double c20, double omega, hipStream_t s);
 
 // ---- setup of levels >= 1
+bool rap_marks(const CoarseLevel& C);
 void rap_from_l0(const FineLevel& L, const CoarseLevel& C, double omega, double* con, uint8_t* done,
                  hipStream_t s);
 void rap_from_lc(const CoarseLevel& F, const CoarseLevel& C, double omega, hipStream_t s);
 void lc_finish(CoarseLevel& C, int32_t* counts, hipStream_t s);    // invD and unknown count
 void lc_to_fp32(CoarseLevel& C, hipStream_t s);
-bool rap_marks(const CoarseLevel& C);
 // compressed operator (slots, interior stencil, table) from the full fp64 arrays
 void lc_compress(CoarseLevel& C, hipStream_t s);
 void l0_to_fp32(FineLevel& L, hipStream_t s);

@@ -785,6 +785,22 @@ static double tridiag_max_eig(const double* a, const double* b, int m) {
     return 0.5 * (lo + hi);
 }
 
+// Largest eigenvalue of the tridiagonal matrix of K Lanczos steps, up to the first vanishing
+// beta.
+static double lanczos_top(const double* alpha, const double* beta, int K) {
+    int m = 0;
+    double amax = 0.0;
+    while (m < K) {
+        amax = std::max(amax, std::fabs(alpha[m]));
+        ++m;
+        if (beta[m - 1] <= 1e-12 * amax) break;
+    }
+    for (int k = 0; k < m; ++k)
+        if (!std::isfinite(alpha[k]) || !std::isfinite(beta[k])) return NAN;
+    return tridiag_max_eig(alpha, beta, m);
+}
+
+
 // Upper end of the spectrum of D^-1 A on level l (the bound that the Chebyshev and the
 // prolongator smoothers need, Section 3.2): the largest Ritz value of Lanczos steps in
 // the D inner product on the symmetric part (A + A^T)/2, started from the SplitMix64
@@ -798,13 +814,40 @@ static double lanczos_lambda(saamg_hierarchy* H, int l, hipStream_t s) {
     const long nb_apply = wide ? l0_wblocks(H->l0, 2) : nb;
     const long n_unk = (l == 0) ? H->l0.n_unknowns : H->lc[l - 1].n_unknowns;
     const int K = (int)std::min<long>(H->opt.eig_iters, n_unk);
-    Tmp t_cur(8 * n), t_prev(8 * n), t_u(8 * n), t_part(sizeof(double) * std::max(nb, nb_apply)),
+    const bool cols = l == 0 && l0_lz_cols(H->l0);
+    const long nb_col = cols ? l0_col_parts(H->l0) : 0;
+    Tmp t_cur(8 * n), t_prev(8 * n), t_u(8 * n), t_next(cols ? 8 * n : 8), t_unext(cols ? 8 * n : 8),
+        t_part(sizeof(double) * std::max({nb, nb_apply, 2 * nb_col})),
         t_scal(sizeof(double) * (S_NSLOTS + 2 * K));
     double* cur = t_cur.as<double>();
     double* prev = t_prev.as<double>();
     double* u = t_u.as<double>();
     double* part = t_part.as<double>();
     double* scal = t_scal.as<double>();
+    std::vector<double> ab(2 * K);
+    if (cols) {
+        // u = the start vector, with vectors of zeros before it; u is S times the last vector
+        // from the first step on
+        double *next = t_next.as<double>(), *un = t_unext.as<double>();
+        l0_lz_start(H->l0, u, part, s);
+        finalize(part, nb, 1, scal, FIN_NORM, 0, s);
+        for (int k = 0; k < K; ++k) {
+            col_lz(H->l0, H->sym, u, cur, prev, next, un, scal, part, s);
+            finalize(part, nb_col, 2, scal, FIN_LZ, S_NSLOTS + 2 * k, s);
+            std::swap(u, un);
+            std::swap(prev, cur);  // prev = the last vector's predecessor, cur = it, next free
+            std::swap(cur, next);
+        }
+        std::vector<double> got(2 * K);
+        HIPCHECK(hipMemcpyAsync(got.data(), scal + S_NSLOTS, sizeof(double) * 2 * K,
+                                hipMemcpyDeviceToHost, s));
+        HIPCHECK(hipStreamSynchronize(s));
+        for (int k = 0; k < K; ++k) {
+            ab[k] = got[2 * k];
+            if (k > 0) ab[K + k - 1] = got[2 * k + 1];
+        }
+        return lanczos_top(ab.data(), ab.data() + K, K);
+    }
     if (l == 0)
         l0_lz_start(H->l0, cur, part, s);
     else
@@ -825,22 +868,10 @@ static double lanczos_lambda(saamg_hierarchy* H, int l, hipStream_t s) {
         finalize(part, nb, 1, scal, FIN_LZ_BETA, S_NSLOTS + K + k, s);
         std::swap(cur, prev);
     }
-    std::vector<double> ab(2 * K);
     HIPCHECK(hipMemcpyAsync(ab.data(), scal + S_NSLOTS, sizeof(double) * 2 * K,
                             hipMemcpyDeviceToHost, s));
     HIPCHECK(hipStreamSynchronize(s));
-    const double* alpha = ab.data();
-    const double* beta = ab.data() + K;
-    int m = 0;
-    double amax = 0.0;
-    while (m < K) {
-        amax = std::max(amax, std::fabs(alpha[m]));
-        ++m;
-        if (beta[m - 1] <= 1e-12 * amax) break;
-    }
-    for (int k = 0; k < m; ++k)
-        if (!std::isfinite(alpha[k]) || !std::isfinite(beta[k])) return NAN;
-    return tridiag_max_eig(alpha, beta, m);
+    return lanczos_top(ab.data(), ab.data() + K, K);
 }
 
 static void free_coarse(CoarseLevel& C);
