@@ -168,6 +168,48 @@ void pool_free(void* p, hipStream_t s) {
 }
 }  // namespace
 
+// The pinned scalars of solve states, one block a state.  To allocate one takes 30 us and to free
+// it 130, most of it a wait for the whole device, of the 1 to 2 ms that a served state lives:
+// up to kHostBlocks freed blocks per device are kept (a page each) and handed out again.  A
+// state that returns its block has waited for its work.
+namespace {
+constexpr size_t kHostBlocks = 64;
+std::mutex g_host_mu;
+std::map<int, std::vector<double*>> g_host_free;
+}  // namespace
+
+static double* host_block(size_t bytes) {
+    int dev = 0;
+    HIPCHECK(hipGetDevice(&dev));
+    {
+        std::lock_guard<std::mutex> g(g_host_mu);
+        auto& f = g_host_free[dev];
+        if (!f.empty()) {
+            double* p = f.back();
+            f.pop_back();
+            return p;
+        }
+    }
+    void* p = nullptr;
+    HIPCHECK(hipHostMalloc(&p, bytes, hipHostMallocDefault));
+    return (double*)p;
+}
+
+static void host_block_free(double* p, int dev) {
+    {
+        std::lock_guard<std::mutex> g(g_host_mu);
+        auto& f = g_host_free[dev];
+        if (f.size() < kHostBlocks) {
+            try {
+                f.push_back(p);
+                return;
+            } catch (...) {
+            }
+        }
+    }
+    (void)hipHostFree(p);
+}
+
 // New buffers are zero-filled on the entry point's stream, in stream order with the work
 // that follows (a null-stream fill would not be ordered with a non-blocking stream).  The
 // fill is a kernel, not a memset, so that no memset node enters a captured graph.
@@ -420,6 +462,8 @@ struct saamg_state {
     double hbuf[S_NSLOTS] = {};
     hipEvent_t ev = nullptr;  // null: the host waits on the stream instead
     int iter = 0, status = SAAMG_OK, done = 0, repl = 0;
+    bool fresh = true;      // no solve yet: the vectors are as allocated, zero
+    bool busy = false;      // between a solve's first launch and a wait for its stream
     bool inflight = false;  // a step is queued whose scalars the host has not read yet
     double bnorm = 0, rel_true = 0, rel_rec = 0;
     double t_ms = 0;
@@ -506,11 +550,14 @@ static void state_alloc(saamg_state* S, saamg_hierarchy* H, bool pinned = true) 
         S->hscal = S->hbuf;
         return;
     }
-    HIPCHECK(hipHostMalloc((void**)&S->hscal, sizeof(double) * S_NSLOTS, hipHostMallocDefault));
+    S->hscal = host_block(sizeof(double) * S_NSLOTS);
     HIPCHECK(hipEventCreateWithFlags(&S->ev, hipEventDisableTiming));
 }
 
 static void state_release(saamg_state* S) {
+    // work that an error left behind may still write the pinned scalars and the vectors
+    if (S->busy) (void)hipDeviceSynchronize();
+    S->busy = false;
     for (double* p : {S->x, S->r, S->q, S->bs}) dfree(p);
     dfree(S->p);
     dfree(S->ring);
@@ -521,7 +568,7 @@ static void state_release(saamg_state* S) {
     S->vd.release();
     dfree(S->part);
     dfree(S->scal);
-    if (S->hscal && S->hscal != S->hbuf) (void)hipHostFree(S->hscal);
+    if (S->hscal && S->hscal != S->hbuf) host_block_free(S->hscal, S->H->device);
     if (S->ev) (void)hipEventDestroy(S->ev);
     S->x = S->r = S->q = S->bs = nullptr;
     S->z = nullptr;
@@ -578,14 +625,17 @@ static void state_start(saamg_state* S, const double* b, const double* x0) {
     scal_start(S->scal, S->tol, S->s);
     S->kdir = 0;
     S->pend = 0;
-    if (S->ringf)  // the direction the first step reads (times beta = 0)
-        zero_fill((char*)S->ring + (size_t)S->pw * ring_index(S, -1) * H->l0.nbox,
-                  (size_t)S->pw * H->l0.nbox, S->s);
-    else
-        zero_fill(S->p, 8 * H->l0.nbox, S->s);
-    // the fused form carries A p in q; the ring form uses q only as scratch for a true
-    // residual
-    if (!S->ringf) zero_fill(S->q, 8 * H->l0.nbox, S->s);
+    // the direction the first step reads (times beta = 0), and A p, which the fused form carries
+    // in q (the ring form uses q only as scratch for a true residual); a new state's are zero
+    if (!S->fresh) {
+        if (S->ringf)
+            zero_fill((char*)S->ring + (size_t)S->pw * ring_index(S, -1) * H->l0.nbox,
+                      (size_t)S->pw * H->l0.nbox, S->s);
+        else
+            zero_fill(S->p, 8 * H->l0.nbox, S->s);
+        if (!S->ringf) zero_fill(S->q, 8 * H->l0.nbox, S->s);
+    }
+    S->fresh = false;
     read_scal(S);
     const double rr = S->hscal[S_RR], bb = S->hscal[S_BB];
     S->bnorm = std::sqrt(bb);
@@ -1640,6 +1690,10 @@ int saamg_destroy(saamg_hierarchy* H) {
     if (!H) return SAAMG_OK;
     // no queued work uses H any more (solves return complete, states are destroyed first)
     MemScope ms(H->mem, nullptr);
+    if (H->ws) {
+        state_release(H->ws);
+        delete H->ws;
+    }
     FineLevel& L = H->l0;
     for (void* p : {(void*)L.unk, (void*)L.irr, (void*)L.base, (void*)L.base_full,
                     (void*)L.zinfo, (void*)L.tiles, (void*)L.tab64, (void*)L.tab32, (void*)L.sigma, (void*)H->Ainv,
@@ -1647,10 +1701,6 @@ int saamg_destroy(saamg_hierarchy* H) {
         dfree(p);
     for (auto& C : H->lc) free_coarse(C);
     drop_operator(H);
-    if (H->ws) {
-        state_release(H->ws);
-        delete H->ws;
-    }
     delete H;
     return SAAMG_OK;
 }
@@ -1720,6 +1770,7 @@ int saamg_solve(saamg_hierarchy* H, const double* d_b, const double* d_x0, doubl
         S.s = (hipStream_t)stream;
         S.tol = tol;
         S.max_iter = max_iter;
+        S.busy = true;
         state_start(&S, d_b, d_x0);
         while (!S.done) {
             state_enqueue(&S);
@@ -1727,6 +1778,7 @@ int saamg_solve(saamg_hierarchy* H, const double* d_b, const double* d_x0, doubl
         }
         cg_unscale(cg_op(H), S.x, d_x, S.s);
         HIPCHECK(hipStreamSynchronize(S.s));
+        S.busy = false;
         S.s = nullptr;  // the caller's stream is not kept beyond the call
         S.t_ms = ms_since(t0);
         state_fill_result(&S, res);
