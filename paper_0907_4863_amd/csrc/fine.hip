@@ -642,22 +642,17 @@ __global__ void __launch_bounds__(kScanT) k_scan_sums(const int32_t* __restrict_
 
 // bs[0 .. nb) <- exclusive scan in place; *total <- the sum (one workgroup of 1024).
 __global__ void __launch_bounds__(1024) k_scan_top(int64_t* bs, long nb, int64_t* total) {
-    __shared__ int64_t part[1024];
+    __shared__ int64_t part[1024 / kWave];
     const int t = threadIdx.x;
     const long chunk = (nb + 1023) / 1024;
     const long a = t * chunk, b = min(nb, a + chunk);
     int64_t s = 0;
     for (long i = a; i < b; ++i) s += bs[i];
-    part[t] = s;
-    __syncthreads();
-    if (t == 0) {
-        int64_t acc = 0;
-        for (int k = 0; k < 1024; ++k) {
-            const int64_t v = part[k];
-            part[k] = acc;
-            acc += v;
-        }
-        *total = acc;
+    int64_t in = s;  // inclusive over the wavefront
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        const int64_t v = __shfl_up(in, o);
+        if ((t & 63) >= o) in += v;
     }
     __syncthreads();
     int64_t acc = part[t];
