@@ -2,6 +2,8 @@
 // structured Galerkin product that builds them, the compression the solve kernels read
 // them in (interior stencil, per-node slot, table of the other rows; also for the
 // transpose of nonsymmetric levels), and the coarsest-level solvers.
+#include <cstring>
+
 #include "march.h"
 
 namespace saamg {
@@ -1221,10 +1223,10 @@ void lc_to_fp32(CoarseLevel& C, hipStream_t s) {
 }
 
 // Compression of a level's operator (after lc_finish).  Pass 1: slot -2 at nodes that are
-// not unknowns, -1 where the row equals the reference row `ref` bit for bit (ref < 0:
-// none does), -3 where the row equals, bit for bit, the row of the node one plane below
-// (which then has a table row of its own or shares one further down), else a new table
-// row; per-64 counts of new rows.  Pass 2: table slots of the new rows in storage order,
+// not unknowns, -1 where the row equals the reference row `ref` bit for bit (none does
+// where that node is not an unknown), -3 where the row equals, bit for bit, the row of the
+// node one plane below (which then has a table row of its own or shares one further down),
+// else a new table row; per-64 counts of new rows.  Pass 2: table slots of the new rows in storage order,
 // and their table rows.  Pass 3: each column, walked up along z, gives its -3 nodes the
 // slot of the node below.  A pipe whose cross-section does not change along z repeats
 // almost every row from plane to plane, so the table holds a few rows per column of the
@@ -1240,7 +1242,7 @@ __global__ void k_lc_classify(LCView<double> c, long n, long ref, int32_t* __res
     if (t < n) {
         int sv = -2;
         if (c.invD[t] != 0.0) {
-            bool same = ref >= 0;
+            bool same = c.invD[ref] != 0.0;
             for (int k = 0; k < 27 && same; ++k) same = lc_full(c, t, k) == lc_full(c, ref, k);
             if (same) {
                 sv = -1;
@@ -1339,33 +1341,47 @@ __global__ void k_lc_fillT(LCView<double> c, long n, const int32_t* __restrict__
     tab[(long)kLcRow * s + 27] = 0.0;
 }
 
-__global__ void k_lc_ref_row(LCView<double> c, long ref, double* out) {
+// The reference row (zeros where the node is not an unknown) and the two totals, in one block for
+// one copy to the host: each copy and wait of its own took 25 us of a level's 300.
+__global__ void k_lc_ref_row(LCView<double> c, long ref, const int64_t* rows, const int64_t* unknowns,
+                             double* out) {
     const int k = threadIdx.x;
-    if (k < 27) out[k] = lc_full(c, ref, k);
+    if (k < 27) out[k] = c.invD[ref] != 0.0 ? lc_full(c, ref, k) : 0.0;
+    if (k == 27) out[k] = __longlong_as_double(rows[0]);
+    if (k == 28) out[k] = __longlong_as_double(unknowns[0]);
 }
 
-void lc_compress(CoarseLevel& C, hipStream_t s) {
+// Compresses C's operator and returns the sum of the n_unk counts of unknowns in `unk`.
+int64_t lc_compress(CoarseLevel& C, const int32_t* unk, long n_unk, hipStream_t s) {
     const long n = C.nstore, nw = (n + 63) / 64;
     // reference row: the node at the centre of the box, if it is an unknown
-    long ref = (C.mx / 2 + 1) + (long)C.sx * (C.my / 2 + 1) + C.sxy * (C.mz / 2 + 1);
-    double dref = 0.0;
-    HIPCHECK(hipMemcpyAsync(&dref, C.invD64 + ref, 8, hipMemcpyDeviceToHost, s));
-    HIPCHECK(hipStreamSynchronize(s));
-    if (dref == 0.0) ref = -1;
-    if (!C.slot) C.slot = (int32_t*)dmalloc(4 * n);
-    int32_t* cnt = (int32_t*)dmalloc(4 * nw);
-    int32_t* base = (int32_t*)dmalloc(4 * nw);
-    int64_t* tot = (int64_t*)dmalloc(8 * scan_words(nw));
-    double* row = (double*)dmalloc(8 * 27);
+    const long ref = (C.mx / 2 + 1) + (long)C.sx * (C.my / 2 + 1) + C.sxy * (C.mz / 2 + 1);
+    if (!C.slot) C.slot = (int32_t*)dmalloc(4 * n, false);
+    int32_t* cnt = (int32_t*)dmalloc(4 * nw, false);
+    int32_t* base = (int32_t*)dmalloc(4 * nw, false);
+    int64_t* tot = (int64_t*)dmalloc(8 * scan_words(nw), false);
+    int64_t* totu = (int64_t*)dmalloc(8 * scan_words(n_unk), false);
+    double* row = (double*)dmalloc(8 * 29, false);
+    const auto release = [&] {
+        for (void* p : {(void*)cnt, (void*)base, (void*)tot, (void*)totu, (void*)row}) dfree(p);
+    };
+    double got[29];
+    int64_t nt = 0, nc = 0;
     try {
         LCView<double> v = C.view<double>();
         hipLaunchKernelGGL(k_lc_classify, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, v, n,
                            ref, C.slot, cnt);
         HIPCHECK(hipGetLastError());
         exclusive_scan(cnt, base, nw, tot, s);
-        int64_t nt = 0;
-        HIPCHECK(hipMemcpyAsync(&nt, tot, 8, hipMemcpyDeviceToHost, s));
+        exclusive_scan(unk, nullptr, n_unk, totu, s);
+        hipLaunchKernelGGL(k_lc_ref_row, dim3(1), dim3(64), 0, s, v, ref, (const int64_t*)tot,
+                           (const int64_t*)totu, row);
+        HIPCHECK(hipGetLastError());
+        HIPCHECK(hipMemcpyAsync(got, row, sizeof(got), hipMemcpyDeviceToHost, s));
         HIPCHECK(hipStreamSynchronize(s));
+        std::memcpy(C.cst64, got, 8 * 27);
+        std::memcpy(&nt, got + 27, 8);
+        std::memcpy(&nc, got + 28, 8);
         if (nt > C.tab_cap) {  // (re)allocate; the fp32 copy follows in lc_to_fp32's caller
             dfree(C.tab64);
             dfree(C.tab32);
@@ -1383,16 +1399,9 @@ void lc_compress(CoarseLevel& C, hipStream_t s) {
         const dim3 gcol((unsigned)((C.sxy + 255) / 256));
         hipLaunchKernelGGL(k_lc_zshare, gcol, dim3(256), 0, s, C.slot, C.sx, C.sy, C.sz);
         HIPCHECK(hipGetLastError());
-        for (int k = 0; k < 27; ++k) C.cst64[k] = 0.0;
-        if (ref >= 0) {
-            hipLaunchKernelGGL(k_lc_ref_row, dim3(1), dim3(64), 0, s, v, ref, row);
-            HIPCHECK(hipGetLastError());
-            HIPCHECK(hipMemcpyAsync(C.cst64, row, 8 * 27, hipMemcpyDeviceToHost, s));
-        }
-        HIPCHECK(hipStreamSynchronize(s));
         if (!C.sym) {
             // the transpose, from the slots just built
-            if (!C.slotT) C.slotT = (int32_t*)dmalloc(4 * n);
+            if (!C.slotT) C.slotT = (int32_t*)dmalloc(4 * n, false);
             v = C.view<double>();
             hipLaunchKernelGGL(k_lc_classifyT, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, v,
                                n, C.slotT, cnt);
@@ -1413,13 +1422,14 @@ void lc_compress(CoarseLevel& C, hipStream_t s) {
                                base, C.tabT_cap, C.slotT, C.tabT64);
             hipLaunchKernelGGL(k_lc_zshare, gcol, dim3(256), 0, s, C.slotT, C.sx, C.sy, C.sz);
             HIPCHECK(hipGetLastError());
-            HIPCHECK(hipStreamSynchronize(s));
         }
+        HIPCHECK(hipStreamSynchronize(s));
     } catch (...) {
-        for (void* p : {(void*)cnt, (void*)base, (void*)tot, (void*)row}) dfree(p);
+        release();
         throw;
     }
-    for (void* p : {(void*)cnt, (void*)base, (void*)tot, (void*)row}) dfree(p);
+    release();
+    return nc;
 }
 
 // Storage indices of the existing nodes of a coarse level, in increasing order.
@@ -1654,7 +1664,7 @@ __global__ void __launch_bounds__(256) k_gjb_update(double* __restrict__ A, int 
 // In-place inverse of the n x n matrix A (row-major, fp64): 2 launches per block of kGjB
 // pivots.
 void dense_invert(double* A, int n, hipStream_t s) {
-    Tmp P(sizeof(double) * kGjB * kGjB), C(sizeof(double) * (size_t)n * kGjB);
+    Tmp P(sizeof(double) * kGjB * kGjB, false), C(sizeof(double) * (size_t)n * kGjB, false);
     const unsigned gcol = (unsigned)((n + 255) / 256);
     const dim3 gup((unsigned)((n + 63) / 64), (unsigned)((n + 15) / 16));
     for (int k0 = 0; k0 < n; k0 += kGjB) {
@@ -1724,6 +1734,8 @@ __global__ void __launch_bounds__(256) k_coarse_solve(const double* __restrict__
     const int row = blockIdx.x * 4 + threadIdx.x / kWave;
     const int lane = threadIdx.x & 63;
     if (row >= nL) return;
+    const double sk = skip ? *skip : 0.0;
+    const long out = cidx[row];
     double acc = 0.0;
     constexpr int U = 6;
     for (int j0 = lane; j0 < nL; j0 += U * kWave) {
@@ -1749,8 +1761,6 @@ __global__ void __launch_bounds__(256) k_coarse_solve(const double* __restrict__
 template <typename TF, typename T>
 void coarse_solve(const double* Ainv, const long* cidx, int nL, const TF* f, T* x, hipStream_t s) {
     KTimer kt_(T_COARSE, s, 8L * nL * nL + nL * (long)(sizeof(TF) + sizeof(T) + 8));
-    const double sk = skip ? *skip : 0.0;
-    const long out = cidx[row];
     klaunch(kt_, true, (k_coarse_solve<TF, T>), dim3((nL + 3) / 4), dim3(256), Ainv, cidx, nL, f,
             x, g_vskip);
     HIPCHECK(hipGetLastError());

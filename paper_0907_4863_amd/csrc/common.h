@@ -178,7 +178,7 @@ struct VSkipScope {
 
 // Allocates through the thread's MemScope and zero-fills on its stream (stream-ordered);
 // throws ApiError(NOMEM) on failure.
-void* dmalloc(size_t bytes);
+void* dmalloc(size_t bytes, bool fill = true);
 void dfree(void* p);
 
 // A temporary device buffer of one step, returned to the allocator when the step's scope
@@ -186,7 +186,8 @@ void dfree(void* p);
 // normal exit; an allocator's stream-ordered reuse covers the exceptional one.
 struct Tmp {
     void* p = nullptr;
-    explicit Tmp(size_t bytes) : p(dmalloc(bytes)) {}
+    // fill = false: the step writes all of it before it reads any
+    explicit Tmp(size_t bytes, bool fill = true) : p(dmalloc(bytes, fill)) {}
     ~Tmp() { dfree(p); }
     Tmp(const Tmp&) = delete;
     Tmp& operator=(const Tmp&) = delete;

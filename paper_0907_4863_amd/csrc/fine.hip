@@ -654,8 +654,14 @@ __global__ void __launch_bounds__(1024) k_scan_top(int64_t* bs, long nb, int64_t
         const int64_t v = __shfl_up(in, o);
         if ((t & 63) >= o) in += v;
     }
+    if ((t & 63) == 63) part[t >> 6] = in;
     __syncthreads();
-    int64_t acc = part[t];
+    int64_t acc = in - s, all = 0;
+    for (int w = 0; w < 1024 / kWave; ++w) {
+        if (w < (t >> 6)) acc += part[w];
+        all += part[w];
+    }
+    if (t == 0) *total = all;
     for (long i = a; i < b; ++i) {
         const int64_t v = bs[i];
         bs[i] = acc;
@@ -943,8 +949,8 @@ __global__ void __launch_bounds__(kThreads) k_l0_line_copy(long nlines, int nseg
 
 void l0_dedup_table(FineLevel& L, const double* full64, const float* full32, hipStream_t s) {
     const long nlines = (long)L.ny * L.nz;
-    Tmp keep(4 * nlines), same(4 * nlines), off(4 * nlines), nb(4 * nlines),
-        tot(8 * scan_words(nlines));
+    Tmp keep(4 * nlines, false), same(4 * nlines, false), off(4 * nlines, false), nb(4 * nlines, false),
+        tot(8 * scan_words(nlines), false);
     const dim3 gl((unsigned)((nlines + kBlockY - 1) / kBlockY)), bl(kWave, kBlockY);
     hipLaunchKernelGGL(k_l0_line_info, gl, bl, 0, s, L.view<double>(), (const int32_t*)L.base_full,
                        full64, L.n_irr, keep.as<int32_t>(), same.as<int32_t>());

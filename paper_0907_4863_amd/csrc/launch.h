@@ -334,7 +334,7 @@ void rap_from_lc(const CoarseLevel& F, const CoarseLevel& C, double omega, hipSt
 void lc_finish(CoarseLevel& C, int32_t* counts, hipStream_t s);    // invD and unknown count
 void lc_to_fp32(CoarseLevel& C, hipStream_t s);
 // compressed operator (slots, interior stencil, table) from the full fp64 arrays
-void lc_compress(CoarseLevel& C, hipStream_t s);
+int64_t lc_compress(CoarseLevel& C, const int32_t* unk, long n_unk, hipStream_t s);
 void l0_to_fp32(FineLevel& L, hipStream_t s);
 void lc_unknown_list(const CoarseLevel& C, long* out, int32_t* counter, hipStream_t s);
 

@@ -212,8 +212,10 @@ static void host_block_free(double* p, int dev) {
 
 // New buffers are zero-filled on the entry point's stream, in stream order with the work
 // that follows (a null-stream fill would not be ordered with a non-blocking stream).  The
-// fill is a kernel, not a memset, so that no memset node enters a captured graph.
-void* dmalloc(size_t bytes) {
+// fill is a kernel, not a memset, so that no memset node enters a captured graph.  Without
+// `fill` the buffer is left as it is, for one that is written whole before it is read: a
+// 64 x 64 x 128 setup made 82 fills, 2 us on the device and 3 on the host each.
+void* dmalloc(size_t bytes, bool fill) {
     void* p = nullptr;
     if (bytes == 0) bytes = 8;
     if (g_mem.alloc) {
@@ -229,7 +231,7 @@ void* dmalloc(size_t bytes) {
     } else {
         p = pool_alloc(bytes);
     }
-    if (g_mem.fill) {
+    if (g_mem.fill && fill) {
         try {
             zero_fill(p, bytes, g_mem.s);
         } catch (...) {
@@ -866,8 +868,8 @@ static double lanczos_lambda(saamg_hierarchy* H, int l, hipStream_t s) {
     const int K = (int)std::min<long>(H->opt.eig_iters, n_unk);
     const bool cols = l == 0 && l0_lz_cols(H->l0);
     const long nb_col = cols ? l0_col_parts(H->l0) : 0;
-    Tmp t_cur(8 * n), t_prev(8 * n), t_u(8 * n), t_next(cols ? 8 * n : 8), t_unext(cols ? 8 * n : 8),
-        t_part(sizeof(double) * std::max({nb, nb_apply, 2 * nb_col})),
+    Tmp t_cur(8 * n), t_prev(8 * n), t_u(8 * n),
+        t_part(sizeof(double) * std::max({nb, nb_apply, 2 * nb_col}), false),
         t_scal(sizeof(double) * (S_NSLOTS + 2 * K));
     double* cur = t_cur.as<double>();
     double* prev = t_prev.as<double>();
@@ -878,6 +880,7 @@ static double lanczos_lambda(saamg_hierarchy* H, int l, hipStream_t s) {
     if (cols) {
         // u = the start vector, with vectors of zeros before it; u is S times the last vector
         // from the first step on
+        Tmp t_next(8 * n), t_unext(8 * n);
         double *next = t_next.as<double>(), *un = t_unext.as<double>();
         l0_lz_start(H->l0, u, part, s);
         finalize(part, nb, 1, scal, FIN_NORM, 0, s);
@@ -1032,8 +1035,8 @@ struct DeviceDomain {
     DeviceDomain(const saamg_domain* dom, int variant, bool scan_mask, const DomainPrep* prep, long nbox,
                  hipStream_t s) {
         try {
-            mask = (uint8_t*)dmalloc(nbox);
-            nwidx = (int32_t*)dmalloc(4 * nbox);
+            mask = (uint8_t*)dmalloc(nbox, false);
+            nwidx = (int32_t*)dmalloc(4 * nbox, false);
             // uploads and fills are queued on s, ordered before the kernels that read them; the
             // host arrays outlive the setup's next synchronisation of s
             HIPCHECK(hipMemcpyAsync(mask, dom->mask, nbox, hipMemcpyHostToDevice, s));
@@ -1053,8 +1056,8 @@ struct DeviceDomain {
         }
     }
     void upload(const DomainPrep& D, hipStream_t s) {
-        nwnodes = (int64_t*)dmalloc(8 * std::max<size_t>(D.nw_nodes.size(), 1));
-        nwfrac = (double*)dmalloc(8 * std::max<size_t>(D.nw_frac.size(), 1));
+        nwnodes = (int64_t*)dmalloc(8 * std::max<size_t>(D.nw_nodes.size(), 1), false);
+        nwfrac = (double*)dmalloc(8 * std::max<size_t>(D.nw_frac.size(), 1), false);
         if (!D.nw_nodes.empty()) {
             HIPCHECK(hipMemcpyAsync(nwnodes, D.nw_nodes.data(), 8 * D.nw_nodes.size(),
                                     hipMemcpyHostToDevice, s));
@@ -1067,8 +1070,8 @@ struct DeviceDomain {
     bool form(const saamg_domain* dom, int variant, bool scan_mask, hipStream_t s) {
         const long nxy = (long)dom->nx * dom->ny, n = dom->n_wall;
         const bool open = dom->robin_d > 0.0, cuts = variant != SAAMG_VARIANT_CONST;
-        Tmp node(8 * n), dir(n), sv(8 * n), bad(4);
-        nwfrac = (double*)dmalloc(48 * (n + (open ? 2 * nxy : 0)));
+        Tmp node(8 * n, false), dir(n, false), sv(8 * n, false), bad(4);
+        nwfrac = (double*)dmalloc(48 * (n + (open ? 2 * nxy : 0)), false);
         if (n > 0) {
             HIPCHECK(hipMemcpyAsync(node.p, dom->wall_node, 8 * n, hipMemcpyHostToDevice, s));
             HIPCHECK(hipMemcpyAsync(dir.p, dom->wall_dir, n, hipMemcpyHostToDevice, s));
@@ -1104,7 +1107,7 @@ static void fine_numbers(FineLevel& L, const saamg_domain* dom, const DeviceDoma
     const double sigma0 = 1.0 / std::sqrt(2.0 * ih2[0] + 2.0 * ih2[1] + 2.0 * ih2[2]);
     for (int a = 0; a < 3; ++a) L.c64[a] = -(sigma0 * (1.0 * ih2[a])) * sigma0;
     const long nr = std::max<long>(L.n_irr, 1);
-    Tmp full64(8 * 16 * nr), full32(4 * 16 * nr);
+    Tmp full64(8 * 16 * nr, false), full32(4 * 16 * nr, false);
     l0_build_table(L, dd.mask, dd.nwidx, dd.nwfrac, variant, sigma0, full64.as<double>(),
                    full32.as<float>(), s);
     l0_dedup_table(L, full64.as<double>(), full32.as<float>(), s);
@@ -1131,23 +1134,19 @@ static int64_t galerkin(saamg_hierarchy* H, int l, CoarseLevel& C, double omega,
     std::unique_ptr<Tmp> con, done;
     if (l == 0) {
         if (rap_marks(C)) {
-            con.reset(new Tmp(8 * 27));
-            done.reset(new Tmp((size_t)C.mx * C.my * C.mz));
+            con.reset(new Tmp(8 * 27, false));
+            done.reset(new Tmp((size_t)C.mx * C.my * C.mz, false));
         }
         rap_from_l0(H->l0, C, omega, con ? con->as<double>() : nullptr,
                     done ? done->as<uint8_t>() : nullptr, s);
     } else
         rap_from_lc(H->lc[l - 1], C, omega, s);
     const long nb = (C.nstore + 255) / 256;
-    int32_t* cnt = (int32_t*)dmalloc(4 * 4 * nb);
+    int32_t* cnt = (int32_t*)dmalloc(4 * 4 * nb, false);
     int64_t nc = 0;
     try {
         lc_finish(C, cnt, s);
-        lc_compress(C, s);
-        Tmp tot(8 * scan_words(4 * nb));
-        exclusive_scan(cnt, nullptr, 4 * nb, tot.as<int64_t>(), s);
-        HIPCHECK(hipMemcpyAsync(&nc, tot.p, 8, hipMemcpyDeviceToHost, s));
-        HIPCHECK(hipStreamSynchronize(s));
+        nc = lc_compress(C, cnt, 4 * nb, s);
     } catch (...) {
         (void)hipStreamSynchronize(s);
         dfree(cnt);
@@ -1171,7 +1170,7 @@ static void build_coarse_solver(saamg_hierarchy* H, hipStream_t s) {
     }
     const int nL = H->nL;
     const long nstore = (H->n_levels == 1) ? H->l0.nbox : H->lc.back().nstore;
-    int32_t* cmap = (int32_t*)dmalloc(4 * nstore);
+    int32_t* cmap = (int32_t*)dmalloc(4 * nstore, false);
     try {
         HIPCHECK(hipMemsetAsync(cmap, 0xff, 4 * nstore, s));
         fill_cmap(cmap, H->cidx, nL, s);
@@ -1200,9 +1199,9 @@ static void build_coarse_solver(saamg_hierarchy* H, hipStream_t s) {
 static void coarse_fp32(saamg_hierarchy* H, hipStream_t s) {
     if (H->opt.precision != SAAMG_MIXED) return;
     for (auto& C : H->lc) {
-        if (!C.tab32) C.tab32 = (float*)dmalloc(4 * kLcRow * C.tab_cap);
-        if (C.tabT64 && !C.tabT32) C.tabT32 = (float*)dmalloc(4 * kLcRow * C.tabT_cap);
-        if (!C.invD32) C.invD32 = (float*)dmalloc(4 * C.nstore);
+        if (!C.tab32) C.tab32 = (float*)dmalloc(4 * kLcRow * C.tab_cap, false);
+        if (C.tabT64 && !C.tabT32) C.tabT32 = (float*)dmalloc(4 * kLcRow * C.tabT_cap, false);
+        if (!C.invD32) C.invD32 = (float*)dmalloc(4 * C.nstore, false);
         lc_to_fp32(C, s);
     }
     HIPCHECK(hipStreamSynchronize(s));
@@ -1258,18 +1257,19 @@ static saamg_hierarchy* setup_impl(const saamg_domain* dom, int variant, const s
         L.wide = o.l0_wide == 2 ? 1 : (o.l0_wide == 1 ? 0 : (int)l0_wide_default(nx));
         L.wzb[0] = l0_wide_zb(L, 2, o.l0_planes);
         L.wzb[1] = l0_wide_zb(L, 4, o.l0_planes);
-        L.unk = (uint64_t*)dmalloc(8 * L.nseg);
-        L.irr = (uint64_t*)dmalloc(8 * L.nseg);
-        L.base = (int32_t*)dmalloc(4 * L.nseg);
-        L.base_full = (int32_t*)dmalloc(4 * L.nseg);
-        L.sigma = (double*)dmalloc(8 * nbox);
+        L.unk = (uint64_t*)dmalloc(8 * L.nseg, false);
+        L.irr = (uint64_t*)dmalloc(8 * L.nseg, false);
+        L.base = (int32_t*)dmalloc(4 * L.nseg, false);
+        L.base_full = (int32_t*)dmalloc(4 * L.nseg, false);
+        L.sigma = (double*)dmalloc(8 * nbox, false);
 
         // segment masks of unknowns and irregular rows, table slots
         int64_t tots[2];
         {
             // two totals: the second scan's total sits in the first one's scratch, which it
             // no longer needs when the second scan (queued after it) writes there
-            Tmp cnt_irr(4 * L.nseg), cnt_unk(4 * L.nseg), d_tot(8 * (1 + scan_words(L.nseg)));
+            Tmp cnt_irr(4 * L.nseg, false), cnt_unk(4 * L.nseg, false),
+                d_tot(8 * (1 + scan_words(L.nseg)), false);
             l0_build_masks(L, dd.mask, dd.nwidx, cnt_irr.as<int32_t>(), cnt_unk.as<int32_t>(), s);
             exclusive_scan(cnt_irr.as<int32_t>(), L.base_full, L.nseg, d_tot.as<int64_t>(), s);
             exclusive_scan(cnt_unk.as<int32_t>(), nullptr, L.nseg, d_tot.as<int64_t>() + 1, s);
@@ -1392,7 +1392,7 @@ static const DomainPrep* check_resetup(const saamg_hierarchy* H, const saamg_dom
 static void check_same_rows(const saamg_hierarchy* H, const DeviceDomain& dd, hipStream_t s) {
     const FineLevel& L = H->l0;
     FineLevel T = L;
-    Tmp unk(8 * L.nseg), irr(8 * L.nseg), c1(4 * L.nseg), c2(4 * L.nseg);
+    Tmp unk(8 * L.nseg, false), irr(8 * L.nseg, false), c1(4 * L.nseg, false), c2(4 * L.nseg, false);
     T.unk = unk.as<uint64_t>();
     T.irr = irr.as<uint64_t>();
     l0_build_masks(T, dd.mask, dd.nwidx, c1.as<int32_t>(), c2.as<int32_t>(), s);
@@ -1462,8 +1462,8 @@ static void set_operator_impl(saamg_hierarchy* H, const saamg_domain* dom, hipSt
         op->base = nullptr;
         op->zinfo = nullptr;
         try {
-            op->base = (int32_t*)dmalloc(4 * L.nseg);
-            op->sigma = (double*)dmalloc(8 * L.nbox);
+            op->base = (int32_t*)dmalloc(4 * L.nseg, false);
+            op->sigma = (double*)dmalloc(8 * L.nbox, false);
         } catch (...) {
             for (void* p : {(void*)op->base, (void*)op->sigma}) dfree(p);
             delete op;

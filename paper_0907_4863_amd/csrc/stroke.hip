@@ -490,9 +490,9 @@ __global__ void __launch_bounds__(256) k_shadow(int nz, long words, const uint64
 }
 
 void l0_zinfo(FineLevel& L, hipStream_t s) {
-    if (!L.zinfo) L.zinfo = (uint8_t*)dmalloc(zinfo_bytes(L));
+    if (!L.zinfo) L.zinfo = (uint8_t*)dmalloc(zinfo_bytes(L), false);
     const long lines = (long)L.ny * L.nz;
-    Tmp compat(lines);
+    Tmp compat(lines, false);
     hipLaunchKernelGGL(k_zcompat, dim3((unsigned)((lines + kBlockY - 1) / kBlockY)),
                        dim3(kWave, kBlockY), 0, s, L.view<double>(), compat.as<uint8_t>());
     hipLaunchKernelGGL(k_zinfo, dim3((unsigned)((zinfo_bytes(L) + 255) / 256)), dim3(256), 0, s,
@@ -528,7 +528,7 @@ void l0_zinfo(FineLevel& L, hipStream_t s) {
         }
         lists.insert(lists.end(), tiles.begin(), tiles.end());
     }
-    L.tiles = (int32_t*)dmalloc(4 * lists.size());
+    L.tiles = (int32_t*)dmalloc(4 * lists.size(), false);
     HIPCHECK(hipMemcpyAsync(L.tiles, lists.data(), 4 * lists.size(), hipMemcpyHostToDevice, s));
     HIPCHECK(hipStreamSynchronize(s));  // the host list goes
 }
