@@ -473,11 +473,13 @@ __global__ void __launch_bounds__(256) k_check_faces(int nx, int ny, int nz, con
 
 // Row n_wall + t (lower end) or n_wall + nxy + t (upper end) of each end-plane unknown.
 __global__ void __launch_bounds__(256) k_end_rows(int nx, int ny, int nz, const uint8_t* __restrict__ mask,
-                                                  long n_wall, int32_t* __restrict__ nwidx) {
+                                                  long n_wall, int64_t* __restrict__ node,
+                                                  int32_t* __restrict__ nwidx) {
     const long nxy = (long)nx * ny, t = blockIdx.x * (long)blockDim.x + threadIdx.x;
     if (t >= nxy) return;
     for (int e = 0; e < 2; ++e) {
         const long i = t + nxy * (e ? nz - 2 : 1);
+        node[n_wall + e * nxy + t] = mask[i] ? i : -1;
         if (mask[i]) nwidx[i] = (int32_t)(n_wall + e * nxy + t);
     }
 }
@@ -519,7 +521,7 @@ __global__ void __launch_bounds__(256) k_fill_one(double* __restrict__ p, long n
     if (t < n) p[t] = 1.0;
 }
 
-void l0_wall_rows(int nx, int ny, int nz, const uint8_t* mask, bool scan_mask, bool open, const int64_t* node,
+void l0_wall_rows(int nx, int ny, int nz, const uint8_t* mask, bool scan_mask, bool open, int64_t* node,
                   const uint8_t* dir, const double* sv, long n_wall, bool cuts, int32_t* nwidx, double* frac,
                   int* bad, hipStream_t s) {
     const long nxy = (long)nx * ny, rows = n_wall + (open ? 2 * nxy : 0);
@@ -530,10 +532,10 @@ void l0_wall_rows(int nx, int ny, int nz, const uint8_t* mask, bool scan_mask, b
         hipLaunchKernelGGL(k_fill_one, dim3((unsigned)((6 * rows + 255) / 256)), dim3(256), 0, s, frac, 6 * rows);
     if (open)
         hipLaunchKernelGGL(k_end_rows, dim3((unsigned)((nxy + 255) / 256)), dim3(256), 0, s, nx, ny, nz, mask,
-                           n_wall, nwidx);
+                           n_wall, node, nwidx);
     if (n_wall > 0)
         hipLaunchKernelGGL(k_wall_rows, dim3((unsigned)((n_wall + 255) / 256)), dim3(256), 0, s, nx, ny,
-                           nxy * nz, mask, node, dir, sv, n_wall, cuts, nwidx, frac, bad);
+                           nxy * nz, mask, (const int64_t*)node, dir, sv, n_wall, cuts, nwidx, frac, bad);
     HIPCHECK(hipGetLastError());
 }
 
@@ -746,21 +748,14 @@ __device__ inline void axis_rule(int variant, bool in_m, bool in_p, double s, do
     }
 }
 
-// Rule of the row at box index i.  Rows without a near-wall entry have the interior
-// stencil.  On a domain with open ends (rob = 2 h_z / d > 0) the unknowns of planes 1
+// Rule of the row at box index i with near-wall row k.  Rows without one have the interior
+// stencil (k < 0, see rule_of).  On a domain with open ends (rob = 2 h_z / d > 0) the unknowns of planes 1
 // and nz-2 are end-plane rows: their outside z-neighbour is u(x'') - (2 h_z / d) u(x)
 // (eq. inlet), and the whole row is halved, which keeps the constant and linear rules
 // symmetric.
-__device__ inline RowRule row_rule(long i, const uint8_t* mask, const int32_t* nwidx,
-                                   const double* nwfrac, int variant, double sigma0,
+__device__ inline RowRule row_rule(long i, long k, const uint8_t* mask, const double* nwfrac, int variant,
                                    const double ih2[3], const long step[3], int nz, double rob) {
     RowRule r;
-    const int k = nwidx[i];
-    if (k < 0) {
-        r.sigma = sigma0;
-        r.f[0] = r.f[1] = r.f[2] = 1.0;
-        return r;
-    }
     const long zp = i / step[2];
     const bool end = rob > 0.0 && (zp == 1 || zp == nz - 2);
     double D = 0.0;
@@ -772,7 +767,7 @@ __device__ inline RowRule row_rule(long i, const uint8_t* mask, const int32_t* n
             dg = 2.0 + rob;
             f = 2.0;
         } else {
-            axis_rule(variant, in_m, in_p, nwfrac[6L * k + 2 * a], nwfrac[6L * k + 2 * a + 1], &dg,
+            axis_rule(variant, in_m, in_p, nwfrac[6 * k + 2 * a], nwfrac[6 * k + 2 * a + 1], &dg,
                       &f);
         }
         D += dg * ih2[a];
@@ -792,56 +787,93 @@ __device__ inline double scaled_off(const RowRule& row, const RowRule& col, int 
     return -(row.sigma * (row.f[a] * ih2[a])) * col.sigma;
 }
 
+// Rules of the near-wall rows (row k: node[k], -1 for an unused one), four values each.
+__global__ void __launch_bounds__(256) k_row_rules(int nx, int ny, int nz, const uint8_t* __restrict__ mask,
+                                                   const int64_t* __restrict__ node, long rows,
+                                                   const double* __restrict__ nwfrac, int variant, double ihx2,
+                                                   double ihy2, double ihz2, double rob,
+                                                   double* __restrict__ rule) {
+    const long k = blockIdx.x * (long)blockDim.x + threadIdx.x;
+    if (k >= rows || node[k] < 0) return;
+    const double ih2[3] = {ihx2, ihy2, ihz2};
+    const long step[3] = {1, (long)nx, (long)nx * ny};
+    const RowRule r = row_rule(node[k], k, mask, nwfrac, variant, ih2, step, nz, rob);
+    double* o = rule + 4 * k;
+    o[0] = r.sigma;
+    o[1] = r.f[0];
+    o[2] = r.f[1];
+    o[3] = r.f[2];
+}
+
+// The rule of a node with near-wall row k (k < 0: none).
+__device__ inline RowRule rule_of(int k, const double* __restrict__ rule, double sigma0) {
+    const double* p = rule + 4L * max(k, 0);
+    RowRule r;
+    r.sigma = k < 0 ? sigma0 : p[0];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) r.f[a] = k < 0 ? 1.0 : p[1 + a];
+    return r;
+}
+
+// sigma at every node and the rows (operator and transpose) of the irregular ones.  Irregular
+// nodes are a few lanes of a wavefront, so its time is that of their trips to memory, two: the
+// masks and near-wall rows of the six neighbours, and the rules of those rows (`rule` holds
+// at least one).  With each neighbour's rule formed from its masks and fractions, seven times
+// two trips one behind the other, 145 x 145 x 435 took 425 us, 131 now and 5 for the rules.
 __global__ void __launch_bounds__(kThreads) k_build_table(
     L0View<double> v, const uint8_t* __restrict__ mask, const int32_t* __restrict__ nwidx,
-    const double* __restrict__ nwfrac, int variant, double sigma0, double ihx2, double ihy2,
-    double ihz2, double rob, long n_irr, double* tab, float* tab32, double* sigma) {
+    const double* __restrict__ rule, double sigma0, double ihx2, double ihy2, double ihz2, long n_irr,
+    double* tab, float* tab32, double* sigma) {
     const double ih2[3] = {ihx2, ihy2, ihz2};
     const long step[3] = {1, (long)v.nx, v.nxy};
     L0_LOOP_BEGIN
     if (inb) {
-        if (!n.unk) {
-            sigma[n.i] = 0.0;
+        if (!n.irr) {  // an interior row has no near-wall row either
+            sigma[n.i] = n.unk ? sigma0 : 0.0;
         } else {
-            const RowRule me =
-                row_rule(n.i, mask, nwidx, nwfrac, variant, sigma0, ih2, step, v.nz, rob);
+            int k[6];
+            bool in[6];
+#pragma unroll
+            for (int d = 0; d < 6; ++d) {
+                const long j = n.i + ((d & 1) ? step[d >> 1] : -step[d >> 1]);
+                in[d] = mask[j] != 0;
+                k[d] = nwidx[j];
+            }
+            const RowRule me = rule_of(nwidx[n.i], rule, sigma0);
+            double fw[8], bw[8];
+#pragma unroll
+            for (int d = 0; d < 8; ++d) fw[d] = bw[d] = 0.0;
+#pragma unroll
+            for (int d = 0; d < 6; ++d) {
+                const RowRule nb = rule_of(k[d], rule, sigma0);
+                fw[d] = in[d] ? scaled_off(me, nb, d >> 1, ih2) : 0.0;
+                bw[d] = in[d] ? scaled_off(nb, me, d >> 1, ih2) : 0.0;
+            }
             sigma[n.i] = me.sigma;
-            if (n.irr) {
-                for (int d = 0; d < 6; ++d) {
-                    const int a = d >> 1;
-                    const long j = n.i + ((d & 1) ? step[a] : -step[a]);
-                    double fw = 0.0, bw = 0.0;
-                    if (mask[j]) {
-                        const RowRule nb =
-                            row_rule(j, mask, nwidx, nwfrac, variant, sigma0, ih2, step, v.nz, rob);
-                        fw = scaled_off(me, nb, a, ih2);
-                        bw = scaled_off(nb, me, a, ih2);
-                    }
-                    tab[8 * n.rank + d] = fw;
-                    tab[8 * (n_irr + n.rank) + d] = bw;
-                    tab32[8 * n.rank + d] = (float)fw;
-                    tab32[8 * (n_irr + n.rank) + d] = (float)bw;
-                }
-                for (int d = 6; d < 8; ++d) {  // padding
-                    tab[8 * n.rank + d] = 0.0;
-                    tab[8 * (n_irr + n.rank) + d] = 0.0;
-                    tab32[8 * n.rank + d] = 0.0f;
-                    tab32[8 * (n_irr + n.rank) + d] = 0.0f;
-                }
+#pragma unroll
+            for (int d = 0; d < 8; ++d) {  // entries 6 and 7 are padding
+                tab[8L * n.rank + d] = fw[d];
+                tab[8 * (n_irr + n.rank) + d] = bw[d];
+                tab32[8L * n.rank + d] = (float)fw[d];
+                tab32[8 * (n_irr + n.rank) + d] = (float)bw[d];
             }
         }
     }
     L0_LOOP_END
 }
 
-void l0_build_table(FineLevel& L, const uint8_t* mask, const int32_t* nwidx, const double* nwfrac,
-                    int variant, double sigma0, double* tab64, float* tab32, hipStream_t s) {
+void l0_build_table(FineLevel& L, const uint8_t* mask, const int32_t* nwidx, const int64_t* node, long rows,
+                    const double* nwfrac, int variant, double sigma0, double* rule, double* tab64,
+                    float* tab32, hipStream_t s) {
     L0View<double> v = L.view<double>();
     v.base = L.base_full;
+    const double ih2[3] = {1.0 / (L.h[0] * L.h[0]), 1.0 / (L.h[1] * L.h[1]), 1.0 / (L.h[2] * L.h[2])};
+    if (rows > 0)
+        hipLaunchKernelGGL(k_row_rules, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, s, L.nx, L.ny,
+                           L.nz, mask, node, rows, nwfrac, variant, ih2[0], ih2[1], ih2[2],
+                           L.robin_d > 0.0 ? 2.0 * L.h[2] / L.robin_d : 0.0, rule);
     hipLaunchKernelGGL(k_build_table, l0_grid(L), dim3(kWave, kBlockY), 0, s, v, mask, nwidx,
-                       nwfrac, variant, sigma0, 1.0 / (L.h[0] * L.h[0]), 1.0 / (L.h[1] * L.h[1]),
-                       1.0 / (L.h[2] * L.h[2]), L.robin_d > 0.0 ? 2.0 * L.h[2] / L.robin_d : 0.0,
-                       L.n_irr, tab64, tab32, L.sigma);
+                       (const double*)rule, sigma0, ih2[0], ih2[1], ih2[2], L.n_irr, tab64, tab32, L.sigma);
     HIPCHECK(hipGetLastError());
 }
 

@@ -107,10 +107,10 @@ void zero_fill(void* p, size_t bytes, hipStream_t s);
 
 // ---- level 0: build
 void l0_scatter_nwidx(int32_t* nwidx, const int64_t* nodes, long n, hipStream_t s);
-// Near-wall rows of the wall entries and open-end planes: nwidx (-1 before) receives the row of
-// each such node, frac (6 per row, n_wall rows and 2 nx ny more with open ends) its wall
-// fractions; *bad (0 before) is set when the domain needs prepare_domain.
-void l0_wall_rows(int nx, int ny, int nz, const uint8_t* mask, bool scan_mask, bool open, const int64_t* node,
+// Near-wall rows of the wall entries and open-end planes, n_wall and with open ends 2 nx ny more:
+// nwidx (-1 before) receives the row of each such node, node (the entries' nodes before) the
+// end planes' nodes or -1, frac (6 per row) the wall fractions; *bad (0 before) is set when the domain needs prepare_domain.
+void l0_wall_rows(int nx, int ny, int nz, const uint8_t* mask, bool scan_mask, bool open, int64_t* node,
                   const uint8_t* dir, const double* sv, long n_wall, bool cuts, int32_t* nwidx, double* frac,
                   int* bad, hipStream_t s);
 void l0_build_masks(FineLevel& L, const uint8_t* mask, const int32_t* nwidx, int32_t* cnt_irr,
@@ -124,8 +124,10 @@ long scan_words(long n);
 void exclusive_scan(const int32_t* in, int32_t* out, long n, int64_t* total, hipStream_t s);
 // The full table (one row per irregular node, slots from base_full) into tab64 / tab32
 // ([2][n_irr][8]) and sigma.
-void l0_build_table(FineLevel& L, const uint8_t* mask, const int32_t* nwidx, const double* nwfrac,
-                    int variant, double sigma0, double* tab64, float* tab32, hipStream_t s);
+// rule: 4 doubles per near-wall row, at least one row.
+void l0_build_table(FineLevel& L, const uint8_t* mask, const int32_t* nwidx, const int64_t* node, long rows,
+                    const double* nwfrac, int variant, double sigma0, double* rule, double* tab64,
+                    float* tab32, hipStream_t s);
 // De-duplicated table of L from the full one: sets L.base, L.n_tab, L.tab64, L.tab32
 // (reallocated).  Synchronises the stream.
 void l0_dedup_table(FineLevel& L, const double* full64, const float* full32, hipStream_t s);

@@ -1027,8 +1027,9 @@ static bool device_checks(const saamg_domain* dom, int variant, bool scan_mask) 
 struct DeviceDomain {
     uint8_t* mask = nullptr;
     int32_t* nwidx = nullptr;
-    int64_t* nwnodes = nullptr;
+    int64_t* nwnodes = nullptr;  // node of each near-wall row (-1: a row not used)
     double* nwfrac = nullptr;
+    long rows = 0;
     // `prep`: the domain's rows when the host has prepared them (a domain that the device's
     // checks cannot take); otherwise the device checks the domain and forms its rows, and
     // prepare_domain has the last word on one that they do not pass
@@ -1046,7 +1047,9 @@ struct DeviceDomain {
             } else if (!form(dom, variant, scan_mask, s)) {
                 const DomainPrep D = prepare_domain(dom, variant, scan_mask);
                 HIPCHECK(hipMemsetAsync(nwidx, 0xff, 4 * nbox, s));
+                dfree(nwnodes);
                 dfree(nwfrac);
+                nwnodes = nullptr;
                 nwfrac = nullptr;
                 upload(D, s);
             }
@@ -1056,6 +1059,7 @@ struct DeviceDomain {
         }
     }
     void upload(const DomainPrep& D, hipStream_t s) {
+        rows = (long)D.nw_nodes.size();
         nwnodes = (int64_t*)dmalloc(8 * std::max<size_t>(D.nw_nodes.size(), 1), false);
         nwfrac = (double*)dmalloc(8 * std::max<size_t>(D.nw_frac.size(), 1), false);
         if (!D.nw_nodes.empty()) {
@@ -1070,14 +1074,16 @@ struct DeviceDomain {
     bool form(const saamg_domain* dom, int variant, bool scan_mask, hipStream_t s) {
         const long nxy = (long)dom->nx * dom->ny, n = dom->n_wall;
         const bool open = dom->robin_d > 0.0, cuts = variant != SAAMG_VARIANT_CONST;
-        Tmp node(8 * n, false), dir(n, false), sv(8 * n, false), bad(4);
-        nwfrac = (double*)dmalloc(48 * (n + (open ? 2 * nxy : 0)), false);
+        rows = n + (open ? 2 * nxy : 0);
+        Tmp dir(n, false), sv(8 * n, false), bad(4);
+        nwnodes = (int64_t*)dmalloc(8 * rows, false);
+        nwfrac = (double*)dmalloc(48 * rows, false);
         if (n > 0) {
-            HIPCHECK(hipMemcpyAsync(node.p, dom->wall_node, 8 * n, hipMemcpyHostToDevice, s));
+            HIPCHECK(hipMemcpyAsync(nwnodes, dom->wall_node, 8 * n, hipMemcpyHostToDevice, s));
             HIPCHECK(hipMemcpyAsync(dir.p, dom->wall_dir, n, hipMemcpyHostToDevice, s));
             HIPCHECK(hipMemcpyAsync(sv.p, dom->wall_s, 8 * n, hipMemcpyHostToDevice, s));
         }
-        l0_wall_rows(dom->nx, dom->ny, dom->nz, mask, scan_mask, open, node.as<int64_t>(),
+        l0_wall_rows(dom->nx, dom->ny, dom->nz, mask, scan_mask, open, nwnodes,
                      dir.as<uint8_t>(), sv.as<double>(), n, cuts, nwidx, nwfrac, bad.as<int>(), s);
         int b = 0;
         HIPCHECK(hipMemcpyAsync(&b, bad.p, 4, hipMemcpyDeviceToHost, s));
@@ -1107,9 +1113,9 @@ static void fine_numbers(FineLevel& L, const saamg_domain* dom, const DeviceDoma
     const double sigma0 = 1.0 / std::sqrt(2.0 * ih2[0] + 2.0 * ih2[1] + 2.0 * ih2[2]);
     for (int a = 0; a < 3; ++a) L.c64[a] = -(sigma0 * (1.0 * ih2[a])) * sigma0;
     const long nr = std::max<long>(L.n_irr, 1);
-    Tmp full64(8 * 16 * nr, false), full32(4 * 16 * nr, false);
-    l0_build_table(L, dd.mask, dd.nwidx, dd.nwfrac, variant, sigma0, full64.as<double>(),
-                   full32.as<float>(), s);
+    Tmp full64(8 * 16 * nr, false), full32(4 * 16 * nr, false), rule(32 * std::max<long>(dd.rows, 1), false);
+    l0_build_table(L, dd.mask, dd.nwidx, dd.nwnodes, dd.rows, dd.nwfrac, variant, sigma0,
+                   rule.as<double>(), full64.as<double>(), full32.as<float>(), s);
     l0_dedup_table(L, full64.as<double>(), full32.as<float>(), s);
 }
 
