@@ -1,5 +1,5 @@
-// Level-0 passes with one stencil, by columns (cols.h): the two passes of a CG step, and the
-// step of the Lanczos estimate.
+// Level-0 passes with one stencil, by columns (cols.h): the two passes of a CG step, the true
+// residual, and the step of the Lanczos estimate.
 //
 // A wavefront marches 3 lines of 62 columns (lanes 0 and 63 are the halo) along z and loads
 // the lines before and after them itself, so that wavefronts share nothing and no plane takes a
@@ -232,6 +232,102 @@ __global__ void __launch_bounds__(kColThreads) k_col_res(StrokeView<double> v,
     if (threadIdx.x == 0 && threadIdx.y == 0) part[blockIdx.x] = s;
 }
 
+// The true residual r = bs - A x with its fp32 copy (r32 not null), and the partials of r.r and
+// bs.bs.  FLUSH: of x' = x + xa p, the update that the last step still owes x, written to xn (the
+// neighbours still read x).
+template <bool FLUSH>
+struct ResidOp {
+    const double *x, *p, *bs;
+    double *xn, *r;
+    float* r32;
+    int b4, b8;
+    double xa;
+    double rr = 0.0, bb = 0.0;
+    double rx[5], rp[5], rb[3], cur[3], val[5];
+    long nxy;
+    __device__ __forceinline__ void start(long nxy_, int zp) {
+        nxy = nxy_;
+        x += nxy * zp;
+        bs += nxy * zp;
+        r += nxy * zp;
+        if (FLUSH) {
+            p += nxy * zp;
+            xn += nxy * zp;
+        }
+        if (r32) r32 += nxy * zp;
+#pragma unroll
+        for (int l = 0; l < 3; ++l) rb[l] = cur[l] = 0.0;
+    }
+    __device__ __forceinline__ void load(const ColAt& at, bool ok) {
+        const auto bx = plane(x, b8, ok), bp = plane(FLUSH ? p : x, b8, ok);
+#pragma unroll
+        for (int l = 0; l < 5; ++l) {
+            bload(bx, at.l8[l], rx[l]);
+            if (FLUSH) bload(bp, at.l8[l], rp[l]);
+        }
+        x += nxy;
+        if (FLUSH) p += nxy;
+    }
+    __device__ __forceinline__ double form(int l) {
+        rx[l] = here(rx[l]);
+        return val[l] = FLUSH ? __builtin_fma(xa, here(rp[l]), rx[l]) : rx[l];
+    }
+    __device__ __forceinline__ void emit(const ColAt& at, bool ok) {
+        // bs of the plane just formed, used when it is the centre
+        const auto b = plane(bs, b8, ok);
+#pragma unroll
+        for (int l = 0; l < 3; ++l) {
+            cur[l] = here(rb[l]);
+            bload(b, at.s8[l], rb[l]);
+        }
+        if (FLUSH) {
+            const auto bn = plane((const double*)xn, b8, ok);
+#pragma unroll
+            for (int l = 0; l < 3; ++l) bstore(bn, at.s8[l], val[l + 1]);
+            xn += nxy;
+        }
+    }
+    __device__ __forceinline__ void body(const ColAt& at, int l, double, double ax) {
+        const double o = cur[l] - ax;
+        bstore(plane((const double*)(r - nxy), b8, true), at.s8[l], o);
+        if (r32) bstore(plane((const float*)(r32 - nxy), b4, true), at.s4[l], (float)o);
+        const bool own = at.s8[l] != kOff;
+        rr += own ? o * o : 0.0;
+        bb += own ? cur[l] * cur[l] : 0.0;
+    }
+    __device__ __forceinline__ void next() {
+        bs += nxy;
+        r += nxy;
+        if (r32) r32 += nxy;
+    }
+};
+
+template <bool FLUSH>
+__global__ void __launch_bounds__(kColThreads) k_col_resid(StrokeView<double> v, const double* __restrict__ bs,
+                                                           const double* __restrict__ x,
+                                                           const double* __restrict__ p,
+                                                           double* __restrict__ xn, double* __restrict__ r,
+                                                           float* __restrict__ r32,
+                                                           const double* __restrict__ scal, double* part) {
+    __shared__ double lds[kColThreads / kWave];
+    ResidOp<FLUSH> op;
+    op.x = x;
+    op.p = p;
+    op.bs = bs;
+    op.xn = xn;
+    op.r = r;
+    op.r32 = r32;
+    op.b4 = (int)(4 * v.nxy);
+    op.b8 = (int)(8 * v.nxy);
+    op.xa = FLUSH ? scal[S_XA] : 0.0;
+    col_march(v, op);
+    const double s0 = block_sum(op.rr, lds), s1 = block_sum(op.bb, lds);
+    if (threadIdx.x == 0 && threadIdx.y == 0) {
+        part[blockIdx.x] = s0;
+        part[gridDim.x + blockIdx.x] = s1;
+    }
+}
+
 // A step of the Lanczos recurrence in one pass: y' = cu u - cc y - cp w, with u = S y and w
 // the vector before y, and u' = S y' for the next step; partials of y' . S y' and y' . y'.
 // S is the symmetric part of A (SP: A itself is not symmetric), the vectors are kept as they
@@ -348,6 +444,16 @@ void col_lz(const FineLevel& L, bool sym, const double* u, const double* y, cons
         hipLaunchKernelGGL(k_col_lz<false>, g, b, 0, s, col_view(L), u, y, w, yn, un, scal, partials);
     else
         hipLaunchKernelGGL(k_col_lz<true>, g, b, 0, s, col_view(L), u, y, w, yn, un, scal, partials);
+    HIPCHECK(hipGetLastError());
+}
+
+void col_resid(const FineLevel& L, const double* bs, const double* x, const double* p, double* xn, double* r,
+               float* r32, const double* scal, double* partials, hipStream_t s) {
+    const dim3 g((unsigned)L.col.blocks()), b(kWave, 4);
+    if (p)
+        hipLaunchKernelGGL(k_col_resid<true>, g, b, 0, s, col_view(L), bs, x, p, xn, r, r32, scal, partials);
+    else
+        hipLaunchKernelGGL(k_col_resid<false>, g, b, 0, s, col_view(L), bs, x, p, xn, r, r32, scal, partials);
     HIPCHECK(hipGetLastError());
 }
 

@@ -51,7 +51,6 @@ bool l0_wide_default(int nx) { return nx % 4 == 0 && nx > 128; }
 // elliptic pipe, one-node against 16-byte lanes, us per launch: fp32 residual 132 -> 107,
 // restriction pass 125 -> 89; fp64 residual 282 -> 204, restriction pass 208 -> 141).
 
-long cg_resid_parts(const FineLevel& L) { return L.wide ? l0_wblocks(L, 2) : l0_blocks(L); }
 long cg_pq_parts(const FineLevel& L, bool ring, int bytes) {
     if (l0_cols(L)) return l0_col_parts(L);
     return ring ? l0_wblocks(L, cg_dir_lanes(bytes)) : l0_blocks(L);
@@ -1502,21 +1501,56 @@ void cg_init(const FineLevel& L, const double* b, const double* x0, double* bs, 
     HIPCHECK(hipGetLastError());
 }
 
-// r = bs - A x; partials of r.r and bs.bs.  ZX: x = 0 (a start without an initial guess),
-// so r = bs and the march reads no stencil operand.
-template <bool ZX>
+// Start of a solve without an initial guess in one pass: b~ as k_cg_init forms it, x = 0, r = b~
+// with its fp32 copy, and the partials of r.r and b~.b~ (k_cg_init and a residual pass: 75 + 56 us
+// at 145 x 145 x 435, 113 now).
+__global__ void __launch_bounds__(kMThreads) k_cg_start(L0View<double> v, const double* __restrict__ sigma,
+                                                       const double* __restrict__ b,
+                                                       double* __restrict__ bs, double* __restrict__ xv,
+                                                       double* __restrict__ r, double* part,
+                                                       float* __restrict__ r32) {
+    __shared__ double lds[kMThreads / kWave];
+    double a0 = 0.0;
+    l0_march<double, false, false>(
+        v, [&](long) { return 0.0; },
+        [&](Idx i, int, int, int, bool, int) { return Vals<double, 2>{{ntl(sigma, i), ntl(b, i)}}; },
+        [&](Idx i, Vals<double, 2> f, double, double, int, int, int z, bool, int) {
+            const double rho = (z == 1 || z == v.nz - 2) ? v.rho_end : 1.0;
+            const double o = f.v[0] * rho * f.v[1];
+            nts(bs, i, o);
+            nts(xv, i, 0.0);
+            nts(r, i, o);
+            if (r32) nts(r32, i, (float)o);
+            a0 += o * o;
+        });
+    const double s0 = block_sum(a0, lds);
+    if (threadIdx.x == 0 && threadIdx.y == 0) {
+        part[blockIdx.x] = s0;
+        part[gridDim.x + blockIdx.x] = s0;
+    }
+}
+
+long cg_start(const FineLevel& L, const double* b, double* bs, double* x, double* r, double* partials,
+              float* r32, hipStream_t s) {
+    hipLaunchKernelGGL(k_cg_start, l0_mgrid(L), dim3(kWave, kMY), 0, s, L.view<double>(), L.sigma, b, bs, x,
+                       r, partials, r32);
+    HIPCHECK(hipGetLastError());
+    return l0_blocks(L);
+}
+
+// r = bs - A x; partials of r.r and bs.bs.
 __global__ void __launch_bounds__(kMThreads) k_cg_resid(L0View<double> v, const double* __restrict__ bs,
                                                        const double* __restrict__ xv,
                                                        double* __restrict__ r, double* part,
                                                        float* __restrict__ r32) {
     __shared__ double lds[kMThreads / kWave];
     double a0 = 0.0, a1 = 0.0;
-    l0_march<double, !ZX, false>(
-        v, [&](Idx j) { return ZX ? 0.0 : at(xv, j); },
+    l0_march<double, true, false>(
+        v, [&](Idx j) { return at(xv, j); },
         [&](Idx i, int, int, int, bool, int) { return Vals<double, 1>{{ntl(bs, i)}}; },
         [&](Idx i, Vals<double, 1> f, double, double ax, int, int, int, bool, int) {
             const double bi = f.v[0];
-            const double o = ZX ? bi : bi - ax;
+            const double o = bi - ax;
             nts(r, i, o);
             if (r32) nts(r32, i, (float)o);
             a0 += o * o;
@@ -1530,20 +1564,21 @@ __global__ void __launch_bounds__(kMThreads) k_cg_resid(L0View<double> v, const 
     }
 }
 
-// x == nullptr: x = 0.
-void cg_resid(const FineLevel& L, const double* bs, const double* x, double* r, double* partials,
+// x == nullptr (on 16-byte lanes): x = 0.  Returns the number of partials per sum.
+long cg_resid(const FineLevel& L, const double* bs, const double* x, double* r, double* partials,
               float* r32, hipStream_t s) {
     if (L.wide) {
         w_cg_resid(L, bs, x, r, partials, r32, s);
-        return;
+        return l0_wblocks(L, 2);
     }
-    if (x)
-        hipLaunchKernelGGL(k_cg_resid<false>, l0_mgrid(L), dim3(kWave, kMY), 0, s,
-                           L.view<double>(), bs, x, r, partials, r32);
-    else
-        hipLaunchKernelGGL(k_cg_resid<true>, l0_mgrid(L), dim3(kWave, kMY), 0, s,
-                           L.view<double>(), bs, (const double*)nullptr, r, partials, r32);
+    if (l0_cols(L)) {
+        col_resid(L, bs, x, nullptr, nullptr, r, r32, nullptr, partials, s);
+        return l0_col_parts(L);
+    }
+    hipLaunchKernelGGL(k_cg_resid, l0_mgrid(L), dim3(kWave, kMY), 0, s, L.view<double>(), bs, x, r, partials,
+                       r32);
     HIPCHECK(hipGetLastError());
+    return l0_blocks(L);
 }
 
 // Direction update with the product by A carried along (fp64 direction):  p <- z + beta p and

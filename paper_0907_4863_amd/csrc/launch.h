@@ -86,7 +86,6 @@ void w_lz_apply(const FineLevel& L, bool sym, const double* vin, const double* s
 // each of them runs on (FineLevel::wide: see the launchers): cg_resid, cg_pq (fp32 z or
 // not), cg_xr, and the V-cycle's fused r . z (its last Chebyshev step, or l0_dot) in a
 // working precision of `bytes` bytes.
-long cg_resid_parts(const FineLevel& L);
 long cg_pq_parts(const FineLevel& L, bool ring, int bytes);
 long cg_xr_parts(const FineLevel& L, bool ring, int bytes);
 long l0_dot_parts(const FineLevel& L, int bytes);
@@ -176,6 +175,9 @@ void l0_up(const FineLevel& L, const CoarseLevel& C, const T* vc, const T* x, co
 long l0_stroke_parts(const FineLevel& L, int bytes);
 
 // ---- level 0, the CG passes by columns (cgcols.hip), over l0_col_parts blocks
+// r = bs - A x by columns; with p, of x + scal[S_XA] p, which goes to xn.
+void col_resid(const FineLevel& L, const double* bs, const double* x, const double* p, double* xn, double* r,
+               float* r32, const double* scal, double* partials, hipStream_t s);
 // One pass per Lanczos step on level 0 (cgcols.hip), for boxes whose planes a 32-bit byte offset
 // reaches.
 bool l0_lz_cols(const FineLevel& L);
@@ -257,7 +259,10 @@ void w_cg_xr(const FineLevel& L, const E* p, double* r, float* r32, const double
 void cg_init(const FineLevel& L, const double* b, const double* x0, double* bs, double* x,
              hipStream_t s);
 // r32 (nullable): fp32 copy of the residual for the fp32 V-cycle
-void cg_resid(const FineLevel& L, const double* bs, const double* x, double* r, double* partials,
+// Both return the number of partials per sum.
+long cg_start(const FineLevel& L, const double* b, double* bs, double* x, double* r, double* partials,
+              float* r32, hipStream_t s);
+long cg_resid(const FineLevel& L, const double* bs, const double* x, double* r, double* partials,
               float* r32, hipStream_t s);
 // Direction update, the product by A and the partials of p . q in one pass, with the
 // q-recursion and an fp64 direction (z in the working precision); cg_xr then takes
