@@ -1515,166 +1515,211 @@ void dense_from_lc(const CoarseLevel& C, const long* cidx, const int32_t* cmap, 
     HIPCHECK(hipGetLastError());
 }
 
-// In-place inversion of the coarsest operator A (row-major n x n, fp64) by Gauss-Jordan
-// elimination without pivoting (A is positive definite, or has a positive definite
-// symmetric part, so every pivot is positive), taken in blocks of kGjB pivots.  For the
-// block K = [k0, k0 + kb), with P = (A_KK)^-1:
+// Inversion of the coarsest operator A (row-major n x n, fp64) by Gauss-Jordan elimination without
+// pivoting (A is positive definite, or has a positive definite symmetric part, so every pivot
+// is positive), taken in blocks of kGjB pivots.  For the block K = [k0, k0 + kb), with
+// P = (A_KK)^-1:
 //   A_Kj <- P A_Kj (j outside K),  A_ij <- A_ij - A_iK A_Kj (new)  and  A_iK <- -A_iK P
 //   (i outside K),  A_KK <- P,
-// which is kb single-pivot steps applied at once.  Two launches per block: the first
-// inverts A_KK in LDS (every workgroup, the same arithmetic), forms the block row on the
-// matrix cores and saves the old block column; the second does the rank-kb update on the
-// matrix cores.
+// which is kb single-pivot steps applied at once.  One launch per block, from one copy of A to
+// another: every workgroup forms the block row of its columns for itself on the matrix cores
+// (the result is laid out as the operand of the update it goes into), and one workgroup
+// beside them updates the next diagonal block first and inverts it, so that the chain of
+// pivots, which bounds the inversion of the few hundred rows there are, runs beside the
+// update and needs one launch a block (a launch for the inversion and the block row and one
+// for the update, in place: 17.6 + 6.4 us a block at 700 rows; 15.3 now).
 constexpr int kGjB = 32;
 
 typedef double gj_d4 __attribute__((ext_vector_type(4)));
 
-// Block step, part 1 (1024 threads).  Every workgroup inverts A_KK in LDS, one thread per
-// element of the kGjB x kGjB block and one barrier per pivot (the block is double-buffered:
-// pivot p reads buffer p % 2 and writes the other); entries past kb stay zero.  The next
-// pivot's reciprocal is formed by the thread that holds it: with every wavefront dividing for
-// itself, four divisions a SIMD and step, the launch took 20.2 us at 700 rows, 17.6 now, of
-// which 9 are the loads, the matrix products and the launch.  (Four wavefronts with the
-// block in registers 19.2, one element a thread in registers 18.3, blocks of 64 pivots 50.)
-// Then:
-//  * wavefront w forms the block row P A_Kj for the 16 columns j0 = 256 g + 16 w (outside
-//    the block) on the matrix cores, as two 16 x 16 tiles of kGjB / 4 steps each;
-//  * rows i = 256 g + t / 4 (outside the block) copy their old block-column entries to C
-//    (n x kGjB, 8 per thread, zero past kb);
-//  * workgroup 0 stores P (kGjB x kGjB, zero past kb).
-// Every global load is issued before the inversion.  Matrix-core operand layouts: see
-// k_gjb_update.
-__global__ void __launch_bounds__(1024) k_gjb_panel(double* __restrict__ A, int n, int k0, int kb,
-                                                    double* __restrict__ Pout,
-                                                    double* __restrict__ C) {
-    __shared__ double M[2][kGjB][kGjB + 1];
-    __shared__ double inv[2];  // reciprocal of the pivot of the step that reads buffer b
-    const int t = threadIdx.x, r = t / kGjB, c = t % kGjB;
-    const int lane = t & 63, w = t >> 6, lr = lane & 15, lk = lane >> 4;
-    const bool in = r < kb && c < kb;
-    const double m0 = in ? A[(long)(k0 + r) * n + k0 + c] : 0.0;
-    M[0][r][c] = m0;
-    if (t == 0) inv[0] = 1.0 / m0;
-    // block-row operands: column jb of the old block row, rows 4 m + lk
-    const int j0 = blockIdx.x * 256 + 16 * w, jb = j0 + lr;
-    const bool tile = j0 < n && !(j0 >= k0 && j0 < k0 + kb);  // uniform over the wavefront
-    double bo[kGjB / 4];
+// The 16 x 16 tile at (i0, j0) of the matrix after block step K, as accumulator elements (rows
+// i0 + lk + 4 v, column j0 + lr); b: the new block row at the tile's columns.  K is
+// kGjB-aligned and ends at a multiple of 16 or at n, so a tile lies wholly inside or outside
+// the block on each axis.  Operand layouts of v_mfma_f64_16x16x4_f64 (lane l, 16 x 4 times
+// 4 x 16): A[l % 16][l / 16], B[l / 16][l % 16]; accumulator element v of lane l is
+// D[l / 16 + 4 v][l % 16] (rows interleaved by 4 across the lane groups, as measured on
+// gfx950), so elements of D feed the next product as its B operand.
+struct GjTile {
+    const double* A;
+    const double* P;  // kGjB x kGjB, zero past kb
+    int n, k0, kb, lr, lk;
+    double b[kGjB / 4];
+    __device__ __forceinline__ GjTile(const double* A_, const double* P_, int n_, int k0_, int kb_, int lane)
+        : A(A_), P(P_), n(n_), k0(k0_), kb(kb_), lr(lane & 15), lk(lane >> 4) {}
+    __device__ __forceinline__ bool in(int i0) const { return i0 >= k0 && i0 < k0 + kb; }
+    __device__ __forceinline__ void row(int j0) {
+        const int j = j0 + lr;
+        if (in(j0)) {
 #pragma unroll
-    for (int m = 0; m < kGjB / 4; ++m) {
-        const int q = 4 * m + lk;
-        bo[m] = (tile && q < kb && jb < n) ? A[(long)(k0 + q) * n + jb] : 0.0;
-    }
-    // old block column of row ic, entries c8 .. c8 + 7
-    const int ic = blockIdx.x * 256 + t / 4, c8 = 8 * (t % 4);
-    const bool crow = ic < n && (ic < k0 || ic >= k0 + kb);
-    double cv[8];
+            for (int m = 0; m < kGjB / 4; ++m) b[m] = P[(4 * m + lk) * kGjB + (j - k0)];
+            return;
+        }
+        double o[kGjB / 4], p0[kGjB / 4], p1[kGjB / 4];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) cv[e] = (crow && c8 + e < kb) ? A[(long)ic * n + k0 + c8 + e] : 0.0;
-    __syncthreads();
-    for (int p = 0; p < kb; ++p) {
-        const int b = p & 1;
-        const double piv = inv[b], mpc = M[b][p][c], mrp = M[b][r][p], mrc = M[b][r][c];
-        const double pc = mpc * piv;  // scaled pivot row (rounded before use)
-        double v;
-        if (r == p)
-            v = (c == p) ? piv : pc;
-        else
-            v = (c == p) ? -mrp * piv : mrc - mrp * pc;
-        M[b ^ 1][r][c] = in ? v : 0.0;
-        if (r == p + 1 && c == p + 1) inv[b ^ 1] = 1.0 / v;
-        __syncthreads();
-    }
-    const int f = kb & 1;  // buffer holding P
-    if (tile) {
+        for (int m = 0; m < kGjB / 4; ++m) {
+            const int q = 4 * m + lk;
+            o[m] = (q < kb && j < n) ? A[(long)(k0 + q) * n + j] : 0.0;
+            p0[m] = P[lr * kGjB + q];
+            p1[m] = P[(16 + lr) * kGjB + q];
+        }
         gj_d4 d0 = {0.0, 0.0, 0.0, 0.0}, d1 = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
         for (int m = 0; m < kGjB / 4; ++m) {
-            d0 = __builtin_amdgcn_mfma_f64_16x16x4f64(M[f][lr][4 * m + lk], bo[m], d0, 0, 0, 0);
-            d1 = __builtin_amdgcn_mfma_f64_16x16x4f64(M[f][16 + lr][4 * m + lk], bo[m], d1, 0, 0, 0);
+            d0 = __builtin_amdgcn_mfma_f64_16x16x4f64(p0[m], o[m], d0, 0, 0, 0);
+            d1 = __builtin_amdgcn_mfma_f64_16x16x4f64(p1[m], o[m], d1, 0, 0, 0);
         }
-        if (jb < n)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int r0 = lk + 4 * v, r1 = 16 + lk + 4 * v;
-                if (r0 < kb) A[(long)(k0 + r0) * n + jb] = d0[v];
-                if (r1 < kb) A[(long)(k0 + r1) * n + jb] = d1[v];
-            }
+        for (int v = 0; v < 4; ++v) {
+            b[v] = d0[v];
+            b[4 + v] = d1[v];
+        }
     }
-    if (crow)
+    __device__ __forceinline__ gj_d4 tile(int i0, int j0) const {
+        gj_d4 out;
+        if (in(i0)) {
+            const bool low = i0 == k0;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) C[(long)ic * kGjB + c8 + e] = cv[e];
-    if (blockIdx.x == 0) Pout[t] = M[f][r][c];
+            for (int v = 0; v < 4; ++v) out[v] = low ? b[v] : b[4 + v];
+            return out;
+        }
+        const int ia = i0 + lr, j = j0 + lr;
+        const bool colK = in(j0);
+        double a[kGjB / 4], cur[4];
+#pragma unroll
+        for (int m = 0; m < kGjB / 4; ++m) {
+            const int q = 4 * m + lk;
+            a[m] = (ia < n && q < kb) ? A[(long)ia * n + k0 + q] : 0.0;
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int i = i0 + lk + 4 * v;
+            cur[v] = (!colK && i < n && j < n) ? A[(long)i * n + j] : 0.0;
+        }
+        gj_d4 s = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int m = 0; m < kGjB / 4; ++m) s = __builtin_amdgcn_mfma_f64_16x16x4f64(a[m], b[m], s, 0, 0, 0);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) out[v] = cur[v] - s[v];
+        return out;
+    }
+};
+
+// Inverse of the kb x kb block in M (zeros past kb) to Pout: 256 threads, thread t holds column
+// t % 32, rows t / 32 + 8 e, and each pivot's row, column and reciprocal (formed by the thread
+// that holds it) pass through LDS, double-buffered, with one barrier per pivot.
+__device__ inline void gj_invert(double (*M)[kGjB + 1], double* lds, int kb, double* __restrict__ Pout) {
+    double(*prow)[kGjB] = reinterpret_cast<double(*)[kGjB]>(lds);
+    double(*pcol)[kGjB] = reinterpret_cast<double(*)[kGjB]>(lds + 2 * kGjB);  // row r at (r % 8) 4 + r / 8
+    double* inv = lds + 4 * kGjB;
+    const int t = threadIdx.x, r = t / kGjB, c = t % kGjB;
+    double m[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) m[e] = M[r + 8 * e][c];
+    if (r == 0) prow[0][c] = m[0];
+    if (c == 0)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) pcol[0][4 * r + e] = m[e];
+    if (t == 0) inv[0] = 1.0 / m[0];
+    __syncthreads();
+#pragma unroll
+    for (int pe = 0; pe < 4; ++pe)
+        for (int p = 8 * pe; p < 8 * pe + 8 && p < kb; ++p) {
+            const int b = p & 1, q = p + 1;
+            const double piv = inv[b], pc = prow[b][c] * piv;  // scaled pivot row (rounded before use)
+            double mc[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) mc[e] = pcol[b][4 * r + e];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if (e == pe && r + 8 * e == p)
+                    m[e] = (c == p) ? piv : pc;
+                else
+                    m[e] = (c == p) ? -mc[e] * piv : m[e] - mc[e] * pc;
+            }
+            const double next = q == 8 * pe + 8 ? m[pe < 3 ? pe + 1 : 3] : m[pe];
+            if (q < kb) {
+                if (r == (q & 7)) {
+                    if (c == q) inv[b ^ 1] = 1.0 / next;
+                    prow[b ^ 1][c] = next;
+                }
+                if (c == q)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) pcol[b ^ 1][4 * r + e] = m[e];
+            }
+            __syncthreads();
+        }
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        Pout[(r + 8 * e) * kGjB + c] = (r + 8 * e < kb && c < kb) ? m[e] : 0.0;
 }
 
-// Block step, part 2, on 16 x 16 tiles, one per wavefront (tile rows i0 = 16 blockIdx.y,
-// columns j0 = 64 blockIdx.x + 16 w).  K is kGjB-aligned and ends at a multiple of 16 or
-// at n, so a tile lies wholly inside or outside the block on each axis.  Outside the
-// block row, S = C_iK B_Kj with B_Kj the new block row (P's columns where j is in K) is
-// formed by v_mfma_f64_16x16x4_f64 over kGjB / 4 steps of 4 pivots, and A_ij <- A_ij - S
-// (A_iK <- -S in the block column).  Inside the block row only A_KK <- P is written (part
-// 1 wrote the rest).  Operand layouts of the instruction (lane l, 16 x 4 times 4 x 16):
-// A[l % 16][l / 16], B[l / 16][l % 16]; accumulator element v of lane l is
-// D[l / 16 + 4 v][l % 16] (rows interleaved by 4 across the lane groups, as measured on
-// gfx950).
-__global__ void __launch_bounds__(256) k_gjb_update(double* __restrict__ A, int n, int k0, int kb,
-                                                    const double* __restrict__ P,
-                                                    const double* __restrict__ C) {
+// Block step from A to B (not the same), P for this block and Pn for the next one, which starts at
+// k0 + kGjB.  Workgroup 0 prepares Pn (k0 < 0: of the first block, nothing else is done);
+// the others take 64 columns of 32 rows each, 16 columns a wavefront.
+__global__ void __launch_bounds__(256) k_gj_step(const double* __restrict__ A, double* __restrict__ B, int n,
+                                                 int k0, int strips, const double* __restrict__ P,
+                                                 double* __restrict__ Pn) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int i0 = 16 * blockIdx.y, j0 = 64 * blockIdx.x + 16 * w;
-    if (j0 >= n) return;  // uniform over the wavefront
-    const bool rowK = i0 >= k0 && i0 < k0 + kb, colK = j0 >= k0 && j0 < k0 + kb;
-    const int lr = lane & 15, lk = lane >> 4;
-    if (rowK) {
-        if (colK)
+    const int kb = min(kGjB, n - k0);
+    GjTile g(A, P, n, k0, kb, lane);
+    if (blockIdx.x == 0) {
+        __shared__ double M[kGjB][kGjB + 1];
+        __shared__ double lds[4 * kGjB + 2];
+        const int n0 = k0 < 0 ? 0 : k0 + kGjB, nb = min(kGjB, n - n0);
+        if (nb <= 0) return;
+        const int i0 = n0 + 16 * (w >> 1), j0 = n0 + 16 * (w & 1);
+        gj_d4 d;
+        if (k0 < 0) {
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                const int i = i0 + lk + 4 * v, j = j0 + lr;
-                if (i < n && j < n) A[(long)i * n + j] = P[(i - k0) * kGjB + (j - k0)];
+                const int i = i0 + g.lk + 4 * v, j = j0 + g.lr;
+                d[v] = (i < n && j < n) ? A[(long)i * n + j] : 0.0;
             }
+        } else {
+            g.row(j0);
+            d = g.tile(i0, j0);
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int i = i0 + g.lk + 4 * v, j = j0 + g.lr;
+            M[i - n0][j - n0] = (i < n && j < n) ? d[v] : 0.0;
+        }
+        __syncthreads();
+        gj_invert(M, lds, nb, Pn);
         return;
     }
-    const int ia = i0 + lr;  // this lane's row of the C operand
-    const int jb = j0 + lr;  // this lane's column of the B operand
-    double a[kGjB / 4], b[kGjB / 4];
+    const int b = blockIdx.x - 1, j0 = 64 * (b % strips) + 16 * w, i1 = 32 * (b / strips);
+    if (j0 >= n) return;  // uniform over the wavefront
+    g.row(j0);
 #pragma unroll
-    for (int m = 0; m < kGjB / 4; ++m) {
-        const int c = 4 * m + lk;
-        a[m] = ia < n ? C[(long)ia * kGjB + c] : 0.0;
-        if (colK)
-            b[m] = P[c * kGjB + (jb - k0)];
-        else
-            b[m] = (c < kb && jb < n) ? A[(long)(k0 + c) * n + jb] : 0.0;
-    }
-    double cur[4];
+    for (int h = 0; h < 2; ++h) {
+        const int i0 = i1 + 16 * h;
+        if (i0 >= n) break;
+        const gj_d4 d = g.tile(i0, j0);
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        const int i = i0 + lk + 4 * v;
-        cur[v] = (!colK && i < n && jb < n) ? A[(long)i * n + jb] : 0.0;
-    }
-    gj_d4 s = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int m = 0; m < kGjB / 4; ++m) s = __builtin_amdgcn_mfma_f64_16x16x4f64(a[m], b[m], s, 0, 0, 0);
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        const int i = i0 + lk + 4 * v;
-        if (i < n && jb < n) A[(long)i * n + jb] = cur[v] - s[v];
+        for (int v = 0; v < 4; ++v) {
+            const int i = i0 + g.lk + 4 * v, j = j0 + g.lr;
+            if (i < n && j < n) B[(long)i * n + j] = d[v];
+        }
     }
 }
 
-// In-place inverse of the n x n matrix A (row-major, fp64): 2 launches per block of kGjB
-// pivots.
+// Inverse of the n x n matrix A (row-major, fp64), in place.
 void dense_invert(double* A, int n, hipStream_t s) {
-    Tmp P(sizeof(double) * kGjB * kGjB, false), C(sizeof(double) * (size_t)n * kGjB, false);
-    const unsigned gcol = (unsigned)((n + 255) / 256);
-    const dim3 gup((unsigned)((n + 63) / 64), (unsigned)((n + 15) / 16));
+    Tmp P(2 * sizeof(double) * kGjB * kGjB, false), T(sizeof(double) * (size_t)n * n, false);
+    double *from = A, *to = T.as<double>(), *p = P.as<double>(), *pn = p + kGjB * kGjB;
+    const int strips = (n + 63) / 64, rows = (n + 31) / 32;
+    hipLaunchKernelGGL(k_gj_step, dim3(1), dim3(256), 0, s, (const double*)from, to, n, -1, strips,
+                       (const double*)nullptr, p);
     for (int k0 = 0; k0 < n; k0 += kGjB) {
-        const int kb = std::min(kGjB, n - k0);
-        hipLaunchKernelGGL(k_gjb_panel, dim3(gcol), dim3(1024), 0, s, A, n, k0, kb, P.as<double>(),
-                           C.as<double>());
-        hipLaunchKernelGGL(k_gjb_update, gup, dim3(256), 0, s, A, n, k0, kb,
-                           (const double*)P.as<double>(), (const double*)C.as<double>());
+        hipLaunchKernelGGL(k_gj_step, dim3((unsigned)(1 + strips * rows)), dim3(256), 0, s,
+                           (const double*)from, to, n, k0, strips, (const double*)p, pn);
+        std::swap(from, to);
+        std::swap(p, pn);
     }
     HIPCHECK(hipGetLastError());
+    if (from != A)
+        HIPCHECK(hipMemcpyAsync(A, from, sizeof(double) * (size_t)n * n, hipMemcpyDeviceToDevice, s));
     HIPCHECK(hipStreamSynchronize(s));
 }
 
