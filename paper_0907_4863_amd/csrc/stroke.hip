@@ -24,10 +24,10 @@
 // instructions bound the strokes (about 34 a node for the three stages of the down-stroke, 60%
 // of the issue slots busy on the largest boxes) and, on small boxes, the latency of a plane
 // step (0.45-0.6 us).  Time per V-cycle, step kernels -> down + up stroke:
-//   256 x 256 x 768 ellipse, quadratic rule, fp32   612 -> 128 + 176 us
-//   512^3 open tube, constant rule, fp32           1650 -> 320 + 463 us
-//   128 x 128 x 256 ellipse, quadratic rule, fp64   223 ->  32 +  33 us
-//   97 x 97 x 291 cavity with bore, fp32            118 ->  29 +  38 us
+//   256 x 256 x 768 ellipse, quadratic rule, fp32   612 -> 122 + 176 us
+//   512^3 open tube, constant rule, fp32           1650 -> 308 + 455 us
+//   128 x 128 x 256 ellipse, quadratic rule, fp64   223 ->  28 +  33 us
+//   97 x 97 x 291 cavity with bore, fp32            118 ->  27 +  37 us
 //   33^3 cylinder, fp64                              34 ->  10 +  12 us
 #include "cols.h"
 
