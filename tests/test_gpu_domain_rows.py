@@ -85,3 +85,33 @@ def test_invalid_domains_are_refused(spoil, open_ends, message):
     assert dom.wall_node.size >= 16384
     with pytest.raises(sa.SaamgError, match=message):
         sa.setup(dom, W.VARIANT_QUAD, sa.default_options())
+
+
+@pytest.mark.parametrize("variant", [W.VARIANT_LIN, W.VARIANT_QUAD])
+def test_resetups_take_the_same_rows(variant):
+    print(f"[case] refresh and operator with device rows, variant {variant}", flush=True)
+    dom = sa.domain_for(SHAPES["ell"], 61, 49, 161, open_ends=True)
+    longer = sa.domain_for(W.Shape.ellipse(1.0, 0.6, 4.3), 61, 49, 161, open_ends=True)
+    assert np.array_equal(dom.mask, longer.mask)
+    order = np.random.default_rng(6).permutation(longer.wall_node.size)
+    mixed = _copy(longer, wall_node=longer.wall_node[order], wall_dir=longer.wall_dir[order],
+                  wall_s=longer.wall_s[order])
+    rng = np.random.default_rng(7)
+    b = torch.from_numpy(np.where(dom.mask.reshape(-1) > 0, rng.uniform(0, 1, dom.mask.size), 0.0)).cuda()
+    out = []
+    for d in (longer, mixed):
+        G = sa.setup(dom, variant, sa.default_options())
+        sa.set_operator(G, d)
+        x = torch.zeros_like(b)
+        res = sa.solve(G, b, x, tol=1e-8)
+        assert res["status"] == 0
+        sa.refresh(G, d)
+        dims = sa.hierarchy_info(G)["dims"]
+        out.append([x.cpu().numpy()] + [sa.level_coefficients(G, l, q) for l, q in enumerate(dims)])
+        other = _copy(d)
+        other.mask[80, 24, 30] = 0
+        with pytest.raises(sa.SaamgError, match="unknowns"):
+            sa.refresh(G, other)
+        sa.destroy(G)
+    for got, want in zip(*out):
+        assert np.array_equal(got, want)
