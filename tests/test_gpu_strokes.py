@@ -125,3 +125,26 @@ def test_solve_with_the_cg_passes_by_columns():
         if precision == sa.FP64:
             assert abs(res["iterations"] - o.iterations) <= 1
         sa.destroy(G)
+
+
+@pytest.mark.parametrize("precision", [sa.FP64, sa.MIXED])
+def test_solve_by_columns_goes_on_from_the_true_residual(precision):
+    """The recursive residual falls below a tolerance that the true one cannot meet: the solve
+    forms the true residual (with the update x is still owed, in one pass), goes on from it, and
+    ends at the iteration limit with the x of a solve to 1e-11: within 1e-8, that tolerance times
+    a condition number below 1e3."""
+    shape, dims = W.Shape.ellipse(1.0, 0.9, 1.5), (125, 109, 77)
+    print("[case] CG by columns past the reachable tolerance", precision, flush=True)
+    dom = sa.domain_for(shape, *dims)
+    rng = np.random.default_rng(11)
+    b = torch.from_numpy(np.where(dom.mask.reshape(-1) > 0, rng.uniform(0, 1, dom.mask.size), 0.0)).to("cuda:0")
+    G = sa.setup(dom, W.VARIANT_LIN, sa.default_options(precision=precision))
+    x, y = torch.zeros_like(b), torch.zeros_like(b)
+    assert sa.solve(G, b, x, tol=1e-11)["status"] == 0
+    with_limit = sa.solve(G, b, y, tol=1e-17, max_iter=60)
+    print({k: with_limit[k] for k in ("iterations", "status", "replacements", "rel_res_true")}, flush=True)
+    assert with_limit["replacements"] >= 1
+    assert torch.isfinite(y).all()
+    assert (x - y).norm() <= 1e-8 * x.norm()
+    assert np.all(y.cpu().numpy()[dom.mask.reshape(-1) == 0] == 0)
+    sa.destroy(G)
