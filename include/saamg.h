@@ -170,8 +170,8 @@ typedef struct {
                                           /* its irregular rows, lines repeating the line  */
                                           /* below sharing rows)                           */
     int64_t table_rows_t[SAAMG_MAX_LEVELS]; /* and of A_l^T (nonsymmetric levels)           */
-    /* host wall time of the setup's phases: domain checks (host), level-0 operator (masks,
-       table, scaling), spectral estimates, Galerkin products and their compression, the
+    /* host wall time of the setup's phases: domain checks made by the host (those of large
+       domains run on the device, in the next phase), level-0 operator (masks, table, scaling), spectral estimates, Galerkin products and their compression, the
        coarsest-level solver, fp32 copies */
     double t_setup_phase_ms[6];
     int32_t l0_wide;                      /* 1: level-0 kernels on 16-byte lanes          */

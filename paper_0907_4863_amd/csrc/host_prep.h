@@ -1,5 +1,5 @@
-// Host-side preparation of a discrete domain for the setup: argument checks and the
-// near-wall rows (Section 2: the unknowns next to the wall and their wall fractions).
+// Host-side preparation of a discrete domain for the setup (of small domains, and of those that
+// the checks on the device do not pass): argument checks and the near-wall rows (Section 2: the unknowns next to the wall and their wall fractions).
 // Plain C++ with no HIP dependency, so that it can also be built and checked on its own.
 #pragma once
 

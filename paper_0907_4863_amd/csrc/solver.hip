@@ -2022,6 +2022,7 @@ int saamg_precond_apply(saamg_hierarchy* H, const double* d_r, double* d_z, void
         MemScope ms(H->mem, (hipStream_t)stream);
         saamg_state& S = *workspace(H);
         S.s = (hipStream_t)stream;
+        S.busy = true;
         // the residual buffer must stay zero off the unknowns: copy via the scaled mask
         cg_mask_copy(H->l0, d_r, S.r, S.r32, S.s);
         precond(&S, false);
@@ -2030,6 +2031,7 @@ int saamg_precond_apply(saamg_hierarchy* H, const double* d_r, double* d_z, void
         else
             HIPCHECK(hipMemcpyAsync(d_z, S.z, 8 * H->l0.nbox, hipMemcpyDeviceToDevice, S.s));
         HIPCHECK(hipStreamSynchronize(S.s));
+        S.busy = false;
         S.s = nullptr;
         return (int)SAAMG_OK;
     });
