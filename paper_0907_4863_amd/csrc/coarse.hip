@@ -529,24 +529,28 @@ __global__ void __launch_bounds__(kThreads) k_lc_restrict_sum(LCView<T> f, LCVie
                                                               const T* __restrict__ yv,
                                                               T* __restrict__ fc,
                                                               T* __restrict__ fd) {
-    LC_PROLOGUE
-    if (!inb) return;
-    T acc = 0;
-    for (int dz = 0; dz < 3; ++dz) {
-        const int z = 3 * Z + dz;
-        if (z >= f.mz) break;
-        for (int dy = 0; dy < 3; ++dy) {
-            const int y = 3 * Y + dy;
-            if (y >= f.my) break;
-            const long row = (long)f.sx * (y + 1) + f.sxy * (z + 1) + 1;
-            for (int dx = 0; dx < 3; ++dx) {
-                const int x = 3 * X + dx;
-                if (x < f.mx) acc += yv[row + x];
-            }
-        }
+    const double skip = c.skip ? *c.skip : 0.0;
+    const long t_ = blockIdx.x * (long)blockDim.x + threadIdx.x;
+    if (t_ >= (long)c.mx * c.my) return;
+    const int X = (int)(t_ % c.mx), Y = (int)(t_ / c.mx), Z = blockIdx.y;
+    const long i = (X + 1) + (long)c.sx * (Y + 1) + c.sxy * (Z + 1);
+    // Bound by latency: all 27 values under way together, those beyond the box from the ghost
+    // layer, which holds zeros in every vector that the march reads.  On the first coarse level
+    // of 128 x 128 x 256 (fp64) 4.5 us; 6.7 with a test before each load.
+    T v[27];
+#pragma unroll
+    for (int k = 0; k < 27; ++k) {
+        const int x = min(3 * X + k % 3, f.mx), y = min(3 * Y + k / 3 % 3, f.my),
+                  z = min(3 * Z + k / 9, f.mz);
+        v[k] = yv[(x + 1) + (long)f.sx * (y + 1) + f.sxy * (z + 1)];
     }
+    const T id = c.invD[i];
+    if (skip != 0.0) return;
+    T acc = 0;
+#pragma unroll
+    for (int k = 0; k < 27; ++k) acc += v[k];
     fc[i] = acc;
-    if (fd) fd[i] = c.invD[i] * acc;
+    if (fd) fd[i] = id * acc;
 }
 
 template <typename T>
