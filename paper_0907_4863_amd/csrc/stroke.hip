@@ -498,7 +498,10 @@ void l0_zinfo(FineLevel& L, hipStream_t s) {
     hipLaunchKernelGGL(k_zinfo, dim3((unsigned)((zinfo_bytes(L) + 255) / 256)), dim3(256), 0, s,
                        L.ny, L.nz, (const uint8_t*)compat.as<uint8_t>(), L.zinfo);
     HIPCHECK(hipGetLastError());
-    if (L.stroke[0][0].W != 0) return;  // the unknowns never change
+    if (L.stroke[0][0].W != 0) {  // the unknowns never change
+        HIPCHECK(hipStreamSynchronize(s));  // `compat` goes
+        return;
+    }
     const long words = (long)L.ny * L.nsegx;
     Tmp sh(8 * words);
     std::vector<uint64_t> shadow(words);
