@@ -24,7 +24,7 @@ struct StrokeView {
     const T* tabT;
     T c[3];
     const uint8_t* zinfo;   // [ny][nz + 1], see k_zinfo
-    const int32_t* tiles;   // the tiles of the cross-section that hold unknowns: x + 65536 y
+    const TileAt* tiles;    // the tiles of the cross-section that hold unknowns
     int live, S;            // their number; planes per slab (a multiple of 3)
     const double* skip;
 };
@@ -284,9 +284,9 @@ template <typename T>
 __device__ __forceinline__ void stroke_tile(const StrokeView<T>& v, int* tx, int* ty, int* sz) {
     const unsigned b = blockIdx.x, nb = gridDim.x, q = nb >> 3;
     const unsigned lb = (b < 8 * q) ? (b & 7) * q + (b >> 3) : b;
-    const int32_t t = v.tiles[lb % (unsigned)v.live];
-    *tx = t & 0xffff;
-    *ty = t >> 16;
+    const TileAt t = v.tiles[lb % (unsigned)v.live];
+    *tx = t.x;
+    *ty = t.y;
     *sz = (int)(lb / (unsigned)v.live);
 }
 

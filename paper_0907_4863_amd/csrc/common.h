@@ -230,6 +230,12 @@ struct ChebCoef {
 };
 ChebCoef cheb_coefficients(double lam_hi, double ratio, int degree);
 
+// A tile of the cross-section, by its number along x and along y (a line of 57-node tiles may hold
+// more than 65,536 of them, and so may a column of 6-line tiles).
+struct TileAt {
+    int32_t x, y;
+};
+
 // Blocks of a V-cycle stroke (stroke.hip): wavefronts per block, planes per slab, the tiles of
 // the cross-section that hold unknowns (and where their list starts in FineLevel::tiles), slabs.
 struct StrokeTile {
@@ -254,7 +260,7 @@ struct FineLevel {
     uint8_t* zinfo = nullptr;   // [ny][nz + 1]: which planes share a line's rows (stroke.hip)
     StrokeTile stroke[2][2];    // [fp32, fp64][down, up]
     StrokeTile col;             // blocks of the CG passes by columns (cgcols.hip)
-    int32_t* tiles = nullptr;   // the lists of tiles
+    TileAt* tiles = nullptr;    // the lists of tiles
     long n_irr = 0;             // irregular rows
     long n_tab = 0;             // table rows: lines repeating the line one plane below share
                                 // its rows (see l0_dedup_table)

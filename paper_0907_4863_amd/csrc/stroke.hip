@@ -473,8 +473,8 @@ __global__ void __launch_bounds__(256) k_zinfo(int ny, int nz, const uint8_t* __
 long zinfo_bytes(const FineLevel& L) { return (long)L.ny * (L.nz + 1); }
 
 static StrokeTile stroke_tiling(const FineLevel& L, const std::vector<uint64_t>& shadow, bool up,
-                                int bytes, std::vector<int32_t>* tiles);
-static std::vector<int32_t> live_tiles(const FineLevel& L, const std::vector<uint64_t>& shadow,
+                                int bytes, std::vector<TileAt>* tiles);
+static std::vector<TileAt> live_tiles(const FineLevel& L, const std::vector<uint64_t>& shadow,
                                        int tx, int lines);
 
 // Which nodes of the (x, y) cross-section hold an unknown on any plane: OR of the unknown
@@ -510,17 +510,17 @@ void l0_zinfo(FineLevel& L, hipStream_t s) {
     HIPCHECK(hipGetLastError());
     HIPCHECK(hipMemcpyAsync(shadow.data(), sh.p, 8 * words, hipMemcpyDeviceToHost, s));
     HIPCHECK(hipStreamSynchronize(s));
-    std::vector<int32_t> lists;
+    std::vector<TileAt> lists;
     for (int d = 0; d < 2; ++d)
         for (int up = 0; up < 2; ++up) {
-            std::vector<int32_t> tiles;
+            std::vector<TileAt> tiles;
             StrokeTile& t = L.stroke[d][up];
             t = stroke_tiling(L, shadow, up != 0, d ? 8 : 4, &tiles);
             t.list = (int)lists.size();
             lists.insert(lists.end(), tiles.begin(), tiles.end());
         }
     {
-        const std::vector<int32_t> tiles = live_tiles(L, shadow, kColX, kColLines);
+        const std::vector<TileAt> tiles = live_tiles(L, shadow, kColX, kColLines);
         L.col.live = (int)tiles.size();
         L.col.list = (int)lists.size();
         // 12 planes a slab, 6 where that leaves compute units with less than two blocks (128 x 128
@@ -531,15 +531,16 @@ void l0_zinfo(FineLevel& L, hipStream_t s) {
         }
         lists.insert(lists.end(), tiles.begin(), tiles.end());
     }
-    L.tiles = (int32_t*)dmalloc(4 * lists.size(), false);
-    HIPCHECK(hipMemcpyAsync(L.tiles, lists.data(), 4 * lists.size(), hipMemcpyHostToDevice, s));
+    const size_t bytes = sizeof(TileAt) * lists.size();
+    L.tiles = (TileAt*)dmalloc(bytes, false);
+    HIPCHECK(hipMemcpyAsync(L.tiles, lists.data(), bytes, hipMemcpyHostToDevice, s));
     HIPCHECK(hipStreamSynchronize(s));  // the host list goes
 }
 
 // The tiles of the cross-section that hold an unknown.
-static std::vector<int32_t> live_tiles(const FineLevel& L, const std::vector<uint64_t>& shadow,
+static std::vector<TileAt> live_tiles(const FineLevel& L, const std::vector<uint64_t>& shadow,
                                        int tx, int lines) {
-    std::vector<int32_t> out;
+    std::vector<TileAt> out;
     for (int j = 0; j * lines < L.ny; ++j)
         for (int i = 0; i * tx < L.nx; ++i) {
             const int x0 = i * tx, x1 = std::min(L.nx, x0 + tx), y1 = std::min(L.ny, lines * (j + 1));
@@ -551,7 +552,7 @@ static std::vector<int32_t> live_tiles(const FineLevel& L, const std::vector<uin
                     if (x1 < 64 * q + 64) m &= ~0ull >> (64 * q + 64 - x1);
                     any = m != 0;
                 }
-            if (any) out.push_back(i | (j << 16));
+            if (any) out.push_back({i, j});
         }
     return out;
 }
@@ -569,7 +570,7 @@ static std::vector<int32_t> live_tiles(const FineLevel& L, const std::vector<uin
 // 52.4 / 62.8 us; on the 256 x 256 x 768 ellipse in fp32 with 16 wavefronts 48 planes 169 / 204
 // us, 24 planes 177 / 215, 54 planes 193 / 236.
 static StrokeTile stroke_tiling(const FineLevel& L, const std::vector<uint64_t>& shadow, bool up,
-                                int bytes, std::vector<int32_t>* tiles) {
+                                int bytes, std::vector<TileAt>* tiles) {
     const int tx = up ? kUpX : kDownX;
     StrokeTile best;
     double t_best = 0.0;
@@ -577,7 +578,7 @@ static StrokeTile stroke_tiling(const FineLevel& L, const std::vector<uint64_t>&
         if (bytes == 8 && W == 16) break;  // fp64: 128 registers a lane do not hold the state
         const int per_cu = (bytes == 4 ? 16 : 8) / W;  // blocks that fit a compute unit's registers
         const double a = bytes == 4 ? 0.38 : 0.15, b = bytes == 4 ? 0.20 : 0.36;
-        const std::vector<int32_t> list = live_tiles(L, shadow, tx, 3 * (W - 2));
+        const std::vector<TileAt> list = live_tiles(L, shadow, tx, 3 * (W - 2));
         StrokeTile t;
         t.W = W;
         t.live = (int)list.size();
