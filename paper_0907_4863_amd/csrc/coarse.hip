@@ -1821,14 +1821,4 @@ template void coarse_solve<double, float>(const double*, const long*, int, const
 template void coarse_solve<float, float>(const double*, const long*, int, const float*, float*,
                                          hipStream_t);
 
-__global__ void k_f2d(const float* a, double* b, long n) {
-    const long t = blockIdx.x * (long)blockDim.x + threadIdx.x;
-    if (t < n) b[t] = (double)a[t];
-}
-
-void f2d_copy(const float* a, double* b, long n, hipStream_t s) {
-    hipLaunchKernelGGL(k_f2d, dim3((n + 255) / 256), dim3(256), 0, s, a, b, n);
-    HIPCHECK(hipGetLastError());
-}
-
 }  // namespace saamg

@@ -1764,6 +1764,23 @@ void cg_unscale(const FineLevel& L, const double* x, double* out, hipStream_t s)
     HIPCHECK(hipGetLastError());
 }
 
+// out = a on every box node (0 where not an unknown): the caller's buffer.
+template <typename T>
+__global__ void __launch_bounds__(kThreads) k_unknowns_copy(L0View<double> v, const T* __restrict__ a,
+                                                            double* __restrict__ out) {
+    L0_LOOP_BEGIN
+    if (inb) out[n.i] = n.unk ? (double)a[n.i] : 0.0;
+    L0_LOOP_END
+}
+
+template <typename T>
+void l0_unknowns_copy(const FineLevel& L, const T* a, double* out, hipStream_t s) {
+    hipLaunchKernelGGL((k_unknowns_copy<T>), l0_grid(L), dim3(kWave, kBlockY), 0, s, L.view<double>(), a, out);
+    HIPCHECK(hipGetLastError());
+}
+template void l0_unknowns_copy<double>(const FineLevel&, const double*, double*, hipStream_t);
+template void l0_unknowns_copy<float>(const FineLevel&, const float*, double*, hipStream_t);
+
 __global__ void __launch_bounds__(kMThreads) k_mask_copy(L0View<double> v, const double* __restrict__ a,
                                                         double* __restrict__ b, float* __restrict__ b32) {
     l0_march<double, false, false>(

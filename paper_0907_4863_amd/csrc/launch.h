@@ -290,6 +290,9 @@ void cg_xr_dir(const FineLevel& L, const E* p, double* r, float* r32, const doub
 template <typename TP>
 void cg_xflush(const FineLevel& L, double* x, const TP* p, const double* scal, hipStream_t s);
 void cg_unscale(const FineLevel& L, const double* x, double* out, hipStream_t s);
+// out = a on the unknowns, 0 at the other box nodes
+template <typename T>
+void l0_unknowns_copy(const FineLevel& L, const T* a, double* out, hipStream_t s);
 // out = in on the unknowns (out untouched elsewhere)
 void cg_mask_copy(const FineLevel& L, const double* in, double* out, float* out32, hipStream_t s);
 // partial sums of a . b over level-0 unknowns (one per block of l0_blocks)
@@ -356,7 +359,6 @@ template <typename TF, typename T>
 void coarse_solve(const double* Ainv, const long* cidx, int nL, const TF* f, T* x, hipStream_t s);
 template <typename TF, typename T>
 void coarse_gs(const CoarseLevel& C, const TF* f, T* x, int sweeps, hipStream_t s);
-void f2d_copy(const float* a, double* b, long n, hipStream_t s);
 
 // ---- reporting helpers
 void l0_export_coef(const FineLevel& L, double* out /* device [27][nbox] */, hipStream_t s);

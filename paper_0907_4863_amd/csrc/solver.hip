@@ -2026,10 +2026,11 @@ int saamg_precond_apply(saamg_hierarchy* H, const double* d_r, double* d_z, void
         // the residual buffer must stay zero off the unknowns: copy via the scaled mask
         cg_mask_copy(H->l0, d_r, S.r, S.r32, S.s);
         precond(&S, false);
+        // the strokes' z is 0 off the unknowns only where every value is finite
         if (S.mixed)
-            f2d_copy((const float*)S.z, d_z, H->l0.nbox, S.s);
+            l0_unknowns_copy(H->l0, (const float*)S.z, d_z, S.s);
         else
-            HIPCHECK(hipMemcpyAsync(d_z, S.z, 8 * H->l0.nbox, hipMemcpyDeviceToDevice, S.s));
+            l0_unknowns_copy(H->l0, (const double*)S.z, d_z, S.s);
         HIPCHECK(hipStreamSynchronize(S.s));
         S.busy = false;
         S.s = nullptr;
