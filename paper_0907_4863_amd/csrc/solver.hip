@@ -732,6 +732,16 @@ static void flush_x(saamg_state* S) {
     finalize(S->part, 1, 0, S->scal, FIN_XA_CLEAR, 0, S->s);
 }
 
+// A step that broke down moves nothing (S_XA is 0, its direction may hold Inf or NaN): x
+// receives what the steps before it still owe.  The fused forms owe it nothing more, their
+// direction pass took the last step's update.
+static void flush_broken(saamg_state* S) {
+    if (!S->ringf) return;
+    S->kdir -= 1;
+    S->pend -= 1;
+    flush_x(S);
+}
+
 // ||b - A x||^2 of the updated x, left in r; x receives what it is still owed.
 static double flush_and_residual(saamg_state* S) {
     const FineLevel& L = cg_op(S->H);
@@ -759,14 +769,14 @@ static void state_complete(saamg_state* S) {
     const double pq = S->hscal[S_PQ], rho = S->hscal[S_RHO], rr = S->hscal[S_RR];
     const double alpha = S->hscal[S_ALPHA];
     if (!std::isfinite(pq) || !std::isfinite(rho) || !std::isfinite(alpha)) {
-        flush_x(S);
+        flush_broken(S);
         S->status = SAAMG_NONFINITE;
         S->done = 1;
         S->rel_true = S->rel_rec = NAN;
         return;
     }
     if (pq <= 0.0 || rho <= 0.0) {
-        flush_x(S);
+        flush_broken(S);
         S->status = SAAMG_BREAKDOWN;
         S->done = 1;
         S->rel_true = std::sqrt(true_residual(S, S->q)) / S->bnorm;

@@ -74,3 +74,22 @@ def test_a_residual_beyond_fp32(name):
     assert sa.solve(G, b, x)["status"] == 0
     assert torch.equal(x, x2)
     sa.destroy(G)
+
+
+@pytest.mark.parametrize("name", BOXES)
+@pytest.mark.parametrize("ring", [0, 2])
+def test_x_holds_the_last_iterate_of_a_solve_that_breaks_down(name, ring):
+    """The first step has no finite length, so the last iterate is the initial guess: 0, or x0 up to
+    the rounding of its scaling and back."""
+    print(f"[case] last iterate, {name} ring={ring}", flush=True)
+    dom = sa.domain_for(SHAPE, *BOXES[name])
+    G = sa.setup(dom, W.VARIANT_QUAD, sa.default_options(precision=sa.MIXED, cg_ring=ring))
+    inside = torch.from_numpy(dom.mask.reshape(-1) > 0).cuda()
+    b = 1e150 * inside.double()
+    x = torch.full_like(b, 7.0)
+    assert sa.solve(G, b, x)["status"] == sa.capi.NONFINITE
+    assert torch.all(x == 0)
+    x0 = 0.75 * inside.double()
+    assert sa.solve(G, b, x, x0=x0)["status"] == sa.capi.NONFINITE
+    assert (x - x0).abs().max() <= 4 * 2.0 ** -53 * 0.75
+    sa.destroy(G)
