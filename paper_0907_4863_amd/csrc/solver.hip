@@ -457,8 +457,8 @@ struct saamg_state {
     bool ringf = false;
     VBuf<float> vf;
     VBuf<double> vd;
-    double* part = nullptr;
-    long npart = 0;
+    double* part = nullptr;      // partial sums, in part_mem or (see state_alloc) elsewhere
+    double* part_mem = nullptr;
     double* scal = nullptr;
     double* hscal = nullptr;  // pinned, or hbuf for a state that allocates nothing on the host
     double hbuf[S_NSLOTS] = {};
@@ -512,7 +512,10 @@ static long pc_parts(const saamg_state* S) {
 
 // pinned = false: no pinned host buffer and no event (the allocation-free solve); the
 // scalars are read into the state itself and the host waits on the stream, and every
-// V-cycle vector is taken, so that the sizes the static array serves stay what they were.
+// V-cycle vector is taken, so that the sizes the static array serves stay what they were.  For
+// the same reason the partial sums there take the room of the step kernels' blocks, and where
+// there are more of them beside strokes (launch shapes of long slabs asked for), the
+// restriction scratch, which the strokes do not use.
 static void state_alloc(saamg_state* S, saamg_hierarchy* H, bool pinned = true) {
     S->H = H;
     S->mixed = H->opt.precision == SAAMG_MIXED;
@@ -541,12 +544,16 @@ static void state_alloc(saamg_state* S, saamg_hierarchy* H, bool pinned = true) 
         S->vd.alloc(H, pinned && strokes(H, 8));
         S->bytes += S->vd.bytes(H);
     }
-    S->npart = std::max<long>(l0_blocks(H->l0), 1);
-    if (H->l0.wide)
-        S->npart = std::max(S->npart, std::max(l0_wblocks(H->l0, 2), l0_wblocks(H->l0, 4)));
-    if (strokes(H, S->pw)) S->npart = std::max(S->npart, l0_stroke_parts(H->l0, S->pw));
-    if (l0_cols(H->l0)) S->npart = std::max(S->npart, l0_col_parts(H->l0));
-    S->part = (double*)dmalloc(sizeof(double) * 3 * S->npart);
+    long steps = std::max<long>(l0_blocks(H->l0), 1);
+    if (H->l0.wide) steps = std::max({steps, l0_wblocks(H->l0, 2), l0_wblocks(H->l0, 4)});
+    long most = steps;
+    if (strokes(H, S->pw)) most = std::max(most, l0_stroke_parts(H->l0, S->pw));
+    if (l0_cols(H->l0)) most = std::max(most, l0_col_parts(H->l0));
+    void* yz = S->mixed ? (void*)S->vf.yz : (void*)S->vd.yz;
+    const bool in_yz = !pinned && most > steps && strokes(H, S->pw) &&
+                       24 * most <= S->pw * VBuf<double>::yz_size(H);
+    S->part_mem = (double*)dmalloc(sizeof(double) * 3 * (in_yz ? steps : most));
+    S->part = in_yz ? (double*)yz : S->part_mem;
     S->scal = (double*)dmalloc(sizeof(double) * S_NSLOTS);
     if (!pinned) {
         S->hscal = S->hbuf;
@@ -568,7 +575,7 @@ static void state_release(saamg_state* S) {
     S->r32 = nullptr;
     S->vf.release();
     S->vd.release();
-    dfree(S->part);
+    dfree(S->part_mem);
     dfree(S->scal);
     if (S->hscal && S->hscal != S->hbuf) host_block_free(S->hscal, S->H->device);
     if (S->ev) (void)hipEventDestroy(S->ev);
@@ -576,7 +583,7 @@ static void state_release(saamg_state* S) {
     S->z = nullptr;
     S->p = nullptr;
     S->ring = nullptr;
-    S->part = S->scal = S->hscal = nullptr;
+    S->part = S->part_mem = S->scal = S->hscal = nullptr;
     S->ev = nullptr;
 }
 
