@@ -413,8 +413,22 @@ __global__ void __launch_bounds__(kColThreads) k_col_lz(StrokeView<double> v, co
 // 64 x 64 x 128 cylinder (0.4 million) 15 -> 20 us, 33^3 9 -> 14 us.  On the 16-byte lanes of
 // wide.hip the passes were faster than by columns (256 x 256 x 768, fp32 direction: 138 + 227
 // us against 153 + 246).
-bool l0_cols(const FineLevel& L) {
+//
+// Where lines change along z (see l0_strokes) the rows read again cost more than masks and slots
+// per plane (solves without / with columns): 80 x 80 x 160 straight 1.03, share 0.08 0.96; 97 x 97
+// x 194 0.06 1.02, each plane 0.94; 128 x 128 x 256 0.16 1.01, each plane 0.92.  Long rows gain at any
+// share on boxes of 1 to 3 million nodes (139^3, 257 x 60 x 130 and 291 x 97 x 97 with a change on
+// each plane 1.04), on larger ones below 0.7 (145 x 145 x 290 0.53 1.03, each plane 0.95).
+bool l0_cols_box(const FineLevel& L) {
     return !L.wide && L.n_unknowns >= 600000 && L.nxy * 8 < (long)kOff;
+}
+bool l0_cols(const FineLevel& L) {
+    double most;
+    if (L.nx > 128)
+        most = L.nbox < 3000000 ? 1.0 : 0.7;
+    else
+        most = L.nbox < 2000000 ? 0.05 : 0.3;
+    return l0_cols_box(L) && l0_change(L) <= most;
 }
 long l0_col_parts(const FineLevel& L) { return L.col.blocks(); }
 
@@ -434,8 +448,12 @@ static StrokeView<double> col_view(const FineLevel& L) {
 
 // Boxes on one-node lanes, where a plane is within a 32-bit byte offset: 145 x 145 x 435 ellipse
 // 126 -> 103 us a step, 128 x 128 x 256 with quadratic rows 70 -> 44; 64 x 64 x 128 18 -> 15.  Boxes on
-// 16-byte lanes keep their two passes (256 x 256 x 768: 15 steps 8.2 ms against 8.7 by columns).
-bool l0_lz_cols(const FineLevel& L) { return !L.wide && L.nxy * 8 < (long)kOff; }
+// 16-byte lanes keep their two passes (256 x 256 x 768: 15 steps 8.2 ms against 8.7 by columns), and
+// so do small boxes whose lines change (33^3 cavity 0.80, with open ends 0.95; from 72^3 on 1.05
+// and more).
+bool l0_lz_cols(const FineLevel& L) {
+    return !L.wide && L.nxy * 8 < (long)kOff && (L.nbox >= 350000 || l0_change(L) <= 0.045);
+}
 
 void col_lz(const FineLevel& L, bool sym, const double* u, const double* y, const double* w, double* yn,
             double* un, const double* scal, double* partials, hipStream_t s) {

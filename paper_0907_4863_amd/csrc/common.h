@@ -258,6 +258,9 @@ struct FineLevel {
     int32_t* base = nullptr;    // table slot of each segment's first irregular row
     int32_t* base_full = nullptr;  // the same before de-duplication (one row per node)
     uint8_t* zinfo = nullptr;   // [ny][nz + 1]: which planes share a line's rows (stroke.hip)
+    // of the planes that an aggregate row (3 lines) has unknowns on, the share, beyond the first,
+    // where rows are not those of the plane below: of all aggregate rows, and of the worst
+    double change_mean = 0.0, change_worst = 0.0;
     StrokeTile stroke[2][2];    // [fp32, fp64][down, up]
     StrokeTile col;             // blocks of the CG passes by columns (cgcols.hip)
     TileAt* tiles = nullptr;    // the lists of tiles

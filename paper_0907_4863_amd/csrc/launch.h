@@ -161,6 +161,8 @@ void l0_prolong(const FineLevel& L, const CoarseLevel& C, const T* v, T* x, doub
 // L.zinfo from L's masks and table (allocated on first use)
 void l0_zinfo(FineLevel& L, hipStream_t s);
 long zinfo_bytes(const FineLevel& L);
+// the share of planes where lines change, as the rules of the forms that keep rows take it
+double l0_change(const FineLevel& L);
 // whether the level-0 V-cycle runs as strokes in a precision of `bytes` bytes
 bool l0_strokes(const FineLevel& L, int degree, int bytes);
 // down: x = degree-2 smoothing of f from zero, fc = P^T (f - A x), fd (nullable) = D^-1 fc of
@@ -183,6 +185,7 @@ void col_resid(const FineLevel& L, const double* bs, const double* x, const doub
 bool l0_lz_cols(const FineLevel& L);
 void col_lz(const FineLevel& L, bool sym, const double* u, const double* y, const double* w, double* yn,
             double* un, const double* scal, double* partials, hipStream_t s);
+bool l0_cols_box(const FineLevel& L);  // where they are possible, whatever the lines do
 bool l0_cols(const FineLevel& L);
 long l0_col_parts(const FineLevel& L);
 constexpr int kColX = 62, kColLines = 12;  // columns and lines of a block's tile

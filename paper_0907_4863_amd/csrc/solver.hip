@@ -548,7 +548,7 @@ static void state_alloc(saamg_state* S, saamg_hierarchy* H, bool pinned = true) 
     if (H->l0.wide) steps = std::max({steps, l0_wblocks(H->l0, 2), l0_wblocks(H->l0, 4)});
     long most = steps;
     if (strokes(H, S->pw)) most = std::max(most, l0_stroke_parts(H->l0, S->pw));
-    if (l0_cols(H->l0)) most = std::max(most, l0_col_parts(H->l0));
+    if (l0_cols_box(H->l0)) most = std::max(most, l0_col_parts(H->l0));  // an operator of its own may take them
     void* yz = S->mixed ? (void*)S->vf.yz : (void*)S->vd.yz;
     const bool in_yz = !pinned && most > steps && strokes(H, S->pw) &&
                        24 * most <= S->pw * VBuf<double>::yz_size(H);
@@ -1470,9 +1470,16 @@ static void refresh_impl(saamg_hierarchy* H, const saamg_domain* dom, hipStream_
     // from here on H changes; a failure leaves it unusable (destroy it)
     drop_operator(H);
     H->bytes -= 12L * 16 * L.n_tab;
+    const int bytes = H->opt.precision == SAAMG_MIXED ? 4 : 8;
+    const bool by_strokes = strokes(H, bytes);
     fine_numbers(L, dom, dd, H->variant, s);
     H->bytes += 12L * 16 * L.n_tab;
     dd.release();
+    if (H->ws && strokes(H, bytes) != by_strokes) {  // its vectors are those of the other form
+        state_release(H->ws);
+        delete H->ws;
+        H->ws = nullptr;
+    }
     for (int l = 0; l + 1 < H->n_levels; ++l) {
         H->par[l] = level_params(H, l, s);
         CoarseLevel& C = H->lc[l];

@@ -29,6 +29,8 @@
 //   128 x 128 x 256 ellipse, quadratic rule, fp64   223 ->  28 +  33 us
 //   97 x 97 x 291 cavity with bore, fp32            118 ->  27 +  37 us
 //   33^3 cylinder, fp64                              34 ->  10 +  12 us
+#include <cstring>
+
 #include "cols.h"
 
 namespace saamg {
@@ -470,6 +472,31 @@ __global__ void __launch_bounds__(256) k_zinfo(int ny, int nz, const uint8_t* __
     zinfo[t] = (s ? kZSame : 0) | ((c[z] & 2) ? kZUnk : 0) | ((1 + rep) << kZRep);
 }
 
+// out[2 Y], out[2 Y + 1]: the planes where aggregate row Y's rows change, beyond its first, and its
+// planes with unknowns.
+__global__ void __launch_bounds__(64) k_zchange(int ny, int nz, const uint8_t* __restrict__ zinfo,
+                                                int* __restrict__ out) {
+    const int y0 = 3 * blockIdx.x;
+    int change = 0, planes = 0;
+    for (int z = threadIdx.x; z < nz; z += kWave) {
+        int all = kZSame, any = 0;
+        for (int y = y0; y < min(y0 + 3, ny); ++y) {
+            const int v = zinfo[(long)(nz + 1) * y + z];
+            all &= v;
+            any |= v;
+        }
+        planes += (any & kZUnk) != 0;
+        change += (any & kZUnk) != 0 && !(all & kZSame);
+    }
+    for (int o = kWave / 2; o > 0; o >>= 1) {
+        change += __shfl_xor(change, o);
+        planes += __shfl_xor(planes, o);
+    }
+    if (threadIdx.x != 0) return;
+    out[2 * blockIdx.x] = max(change - 1, 0);
+    out[2 * blockIdx.x + 1] = planes;
+}
+
 long zinfo_bytes(const FineLevel& L) { return (long)L.ny * (L.nz + 1); }
 
 static StrokeTile stroke_tiling(const FineLevel& L, const std::vector<uint64_t>& shadow, bool up,
@@ -497,19 +524,31 @@ void l0_zinfo(FineLevel& L, hipStream_t s) {
                        dim3(kWave, kBlockY), 0, s, L.view<double>(), compat.as<uint8_t>());
     hipLaunchKernelGGL(k_zinfo, dim3((unsigned)((zinfo_bytes(L) + 255) / 256)), dim3(256), 0, s,
                        L.ny, L.nz, (const uint8_t*)compat.as<uint8_t>(), L.zinfo);
+    // the unknowns never change, and with them neither do the tiles: the first time only
+    const bool first = L.stroke[0][0].W == 0;
+    const long nrow = (L.ny + 2) / 3, words = first ? (long)L.ny * L.nsegx : 0;
+    Tmp sh(8 * (words + nrow), first);  // the shadow, then two counts an aggregate row
+    std::vector<uint64_t> got(words + nrow);
+    hipLaunchKernelGGL(k_zchange, dim3((unsigned)nrow), dim3(kWave), 0, s, L.ny, L.nz,
+                       (const uint8_t*)L.zinfo, (int*)(sh.as<uint64_t>() + words));
+    if (first)
+        hipLaunchKernelGGL(k_shadow, dim3((unsigned)((words + 255) / 256), (unsigned)((L.nz + 31) / 32)),
+                           dim3(256), 0, s, L.nz, words, (const uint64_t*)L.unk, sh.as<uint64_t>());
     HIPCHECK(hipGetLastError());
-    if (L.stroke[0][0].W != 0) {  // the unknowns never change
-        HIPCHECK(hipStreamSynchronize(s));  // `compat` goes
-        return;
+    HIPCHECK(hipMemcpyAsync(got.data(), sh.p, 8 * got.size(), hipMemcpyDeviceToHost, s));
+    HIPCHECK(hipStreamSynchronize(s));  // also: the temporaries may go
+    long change = 0, planes = 0;
+    L.change_worst = 0.0;
+    for (long Y = 0; Y < nrow; ++Y) {
+        int n[2];
+        std::memcpy(n, &got[words + Y], 8);
+        change += n[0];
+        planes += n[1];
+        if (n[1]) L.change_worst = std::max(L.change_worst, (double)n[0] / n[1]);
     }
-    const long words = (long)L.ny * L.nsegx;
-    Tmp sh(8 * words);
-    std::vector<uint64_t> shadow(words);
-    hipLaunchKernelGGL(k_shadow, dim3((unsigned)((words + 255) / 256), (unsigned)((L.nz + 31) / 32)),
-                       dim3(256), 0, s, L.nz, words, (const uint64_t*)L.unk, sh.as<uint64_t>());
-    HIPCHECK(hipGetLastError());
-    HIPCHECK(hipMemcpyAsync(shadow.data(), sh.p, 8 * words, hipMemcpyDeviceToHost, s));
-    HIPCHECK(hipStreamSynchronize(s));
+    L.change_mean = planes ? (double)change / planes : 0.0;
+    if (!first) return;
+    const std::vector<uint64_t>& shadow = got;
     std::vector<TileAt> lists;
     for (int d = 0; d < 2; ++d)
         for (int up = 0; up < 2; ++up) {
@@ -625,9 +664,40 @@ static CoarseBox<T> coarse_box(const CoarseLevel& C) {
     return b;
 }
 
-// Strokes need the degree-2 smoother and planes that a 32-bit byte offset reaches.
+// Strokes need the degree-2 smoother and planes that a 32-bit byte offset reaches, and pay where
+// lines keep their rows from plane to plane: a plane where a line changes reads rows in each
+// stage, two dependent trips to memory behind one another, and so do the planes after it.  The line
+// lies where the two forms met, in the share of changing planes (solves of 8 steps, by steps /
+// by strokes, of pipes whose radius changes every few planes, pipes with open ends, cavities with
+// bores, tapers, spheres and pipes along x and y, from 24^3 to 256^3):
+//   below 800 thousand nodes a launch lasts as long as its slowest block, and one change inside a
+//   slab costs what strokes save: 64 x 64 x 128 closed 1.17, with open ends (share 0.03) 1.05,
+//   49 x 49 x 98 with open ends (0.04) 1.02, 40^3 (0.10) 0.98, 33^3 cavity (0.32) 0.85, sphere
+//   0.76, 64 x 64 x 128 cavity (0.08) 0.88, which keeps strokes' fewer launches for batches;
+//   up to 3 million 96 x 96 x 192 with a share of 0.43 1.0, 0.27 1.1, each plane 0.76;
+//   above 128 x 128 x 256 0.71: 1.06, each plane 0.93;
+//   rows longer than 128 nodes that miss the 16-byte lanes are slow by steps: with a change on
+//   each plane 139^3 1.2 in fp64 and 1.0 in fp32, 131 x 131 x 262 and 161 x 161 x 322 1.1 to 1.2,
+//   above 10 million 199 x 199 x 300 0.95 and 1.0;
+//   with 16-byte lanes 256^3 fp64 0.29: 1.0, fp32 0.45: 1.0, each plane 0.66 and 0.83.
+// On one-node lanes a change anywhere holds up the launch, so the worst aggregate row counts
+// as much as the mean (pipes along x, whose lines beside the wall change on every plane).
 bool l0_strokes(const FineLevel& L, int degree, int bytes) {
-    return degree == 2 && L.nxy * bytes < (long)kOff;
+    if (degree != 2 || L.nxy * bytes >= (long)kOff) return false;
+    double most;
+    if (L.nbox < 800000)
+        most = 0.1;
+    else if (L.wide)
+        most = bytes == 8 ? 0.3 : 0.45;
+    else if (L.nx > 128 && L.nbox <= 10000000)
+        most = bytes == 8 || L.nbox >= 3000000 ? 1.0 : 0.75;
+    else
+        most = L.nbox < 3000000 ? 0.4 : 0.75;
+    return l0_change(L) <= most;
+}
+
+double l0_change(const FineLevel& L) {
+    return L.wide ? L.change_mean : 0.5 * (L.change_mean + L.change_worst);
 }
 
 long l0_stroke_parts(const FineLevel& L, int bytes) { return L.stroke[bytes == 8][1].blocks(); }
