@@ -230,8 +230,9 @@ int saamg_domain_from_shape(int kind, double a, double b, double length, double 
  *   stream    work is queued on it (hipStream_t, NULL = default stream); the call
  *             returns after the hierarchy is complete.
  *   *out      owns all device memory of the hierarchy until saamg_destroy.
- * Errors: SAAMG_INVALID_ARG for a bad domain or option (nothing allocated),
- * SAAMG_NOMEM, SAAMG_HIP_ERROR.  Setups, solves and steps of other hierarchies may run
+ * Errors: SAAMG_INVALID_ARG for a bad domain or option (nothing allocated through the
+ * callbacks; without them the checks of a large domain take memory from the library's
+ * pool and return it), SAAMG_NOMEM, SAAMG_HIP_ERROR.  Setups, solves and steps of other hierarchies may run
  * at the same time on other threads and streams of the device.
  */
 int saamg_setup(const saamg_domain* dom, int variant, const saamg_options* opt, void* stream,

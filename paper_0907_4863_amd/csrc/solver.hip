@@ -1254,7 +1254,8 @@ static void coarse_fp32(saamg_hierarchy* H, hipStream_t s) {
 static saamg_hierarchy* setup_impl(const saamg_domain* dom, int variant, const saamg_options* opt,
                                    hipStream_t s) {
     auto t0 = std::chrono::steady_clock::now();
-    const bool on_device = device_checks(dom, variant, true);
+    // a caller's allocator is promised that a domain is checked before anything is allocated
+    const bool on_device = !(opt && opt->alloc) && device_checks(dom, variant, true);
     DomainPrep D;
     if (!on_device) D = prepare_domain(dom, variant);
     const double t_host = ms_since(t0);
