@@ -1283,8 +1283,6 @@ static saamg_hierarchy* setup_impl(const saamg_domain* dom, int variant, const s
         H->variant = variant;
         H->opt = o;
         H->sym = variant != SAAMG_VARIANT_QUAD;
-        DeviceDomain dd(dom, variant, true, on_device ? nullptr : &D, nbox, s);
-        checked = true;
         FineLevel& L = H->l0;
         L.nx = nx;
         L.ny = ny;
@@ -1302,6 +1300,8 @@ static saamg_hierarchy* setup_impl(const saamg_domain* dom, int variant, const s
         L.wide = o.l0_wide == 2 ? 1 : (o.l0_wide == 1 ? 0 : (int)l0_wide_default(nx));
         L.wzb[0] = l0_wide_zb(L, 2, o.l0_planes);
         L.wzb[1] = l0_wide_zb(L, 4, o.l0_planes);
+        DeviceDomain dd(dom, variant, true, on_device ? nullptr : &D, nbox, s);
+        checked = true;
         L.unk = (uint64_t*)dmalloc(8 * L.nseg, false);
         L.irr = (uint64_t*)dmalloc(8 * L.nseg, false);
         L.base = (int32_t*)dmalloc(4 * L.nseg, false);

@@ -48,6 +48,20 @@ def test_nothing_is_allocated_for_a_refused_domain(spoil, message):
     assert (al.n_alloc, al.n_free) == (0, 0)
 
 
+@pytest.mark.parametrize("options,message", [({"l0_wide": 2}, "multiple of 4"), ({"l0_tile_x": 2}, "exceeds")])
+def test_nothing_is_allocated_for_an_option_that_does_not_fit_the_box(options, message):
+    print(f"[case] refused option and the caller's allocator: {message}", flush=True)
+    dom, bad = domain(), domain()
+    face(bad)
+    for alloc in (sa.TorchAllocator(), None):
+        with pytest.raises(sa.SaamgError, match=message):
+            sa.setup(dom, W.VARIANT_QUAD, sa.default_options(allocator=alloc, **options))
+        with pytest.raises(sa.SaamgError, match="face of the box"):  # the domain's errors come first
+            sa.setup(bad, W.VARIANT_QUAD, sa.default_options(allocator=alloc, **options))
+        if alloc is not None:
+            assert (alloc.n_alloc, alloc.n_free) == (0, 0)
+
+
 @pytest.mark.parametrize("open_ends", [False, True])
 def test_the_hierarchy_is_that_of_the_pool(open_ends):
     print(f"[case] the caller's allocator, open={open_ends}", flush=True)
