@@ -284,10 +284,15 @@ def hbm_ceiling() -> dict:
     return {f"{k}_GBs": v for k, v in best.items()}
 
 
+# the sources of the kernels that the timer's classes cover
+KERNEL_SOURCES = ("fine.hip", "wide.hip", "stroke.hip", "cgcols.hip", "coarse.hip", "common.h", "launch.h",
+                  "march.h", "cols.h")
+
+
 def _kernel_sources_digest() -> str:
     import hashlib
     h = hashlib.sha256()
-    for f in ("fine.hip", "wide.hip", "coarse.hip", "common.h", "launch.h", "march.h"):
+    for f in KERNEL_SOURCES:
         with open(os.path.join(ROOT, "paper_0907_4863_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()
