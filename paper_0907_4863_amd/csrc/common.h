@@ -264,6 +264,7 @@ struct FineLevel {
     StrokeTile stroke[2][2];    // [fp32, fp64][down, up]
     StrokeTile col;             // blocks of the CG passes by columns (cgcols.hip)
     TileAt* tiles = nullptr;    // the lists of tiles
+    long n_tiles = 0;           // their entries
     long n_irr = 0;             // irregular rows
     long n_tab = 0;             // table rows: lines repeating the line one plane below share
                                 // its rows (see l0_dedup_table)

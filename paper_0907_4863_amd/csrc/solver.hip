@@ -1325,7 +1325,8 @@ static saamg_hierarchy* setup_impl(const saamg_domain* dom, int variant, const s
         L.n_unknowns = tots[1];
         fine_numbers(L, dom, dd, variant, s);
         dd.release();
-        H->bytes = 24L * L.nseg + 8L * nbox + 12L * 16 * L.n_tab + zinfo_bytes(L);
+        H->bytes = 24L * L.nseg + 8L * nbox + 12L * 16 * L.n_tab + zinfo_bytes(L) +
+                   (long)sizeof(TileAt) * L.n_tiles;
         H->t_phase_ms[0] = t_host;
         H->t_phase_ms[1] = ms_since(t0) - t_host;
 
@@ -1846,13 +1847,17 @@ int saamg_footprint_bytes(int nx, int ny, int nz, int variant, int precision, in
         const bool mixed = precision == SAAMG_MIXED;
         const int na = variant == SAAMG_VARIANT_QUAD ? 27 : 14;
         double h = 8.0 * nbox + 20.0 * nbox / 64 + 0.2 * nbox * 12 * 16;  // sigma, masks, table
+        // line information and tile lists (at most those of the smallest tiles, five times)
+        h += (double)ny * (nz + 1) + 5.0 * sizeof(TileAt) * (nx / 57 + 1.0) * (ny / 6 + 1.0);
         double st = 48.0 * nbox + (mixed ? 4 : 8) * nbox;
         if (l0_wide_default(nx)) {  // the ring of directions in place of the fp64 direction
             const int pw = mixed ? 4 : 8;
             st += (double)(pw * cg_ring_len((long)nbox, pw) - 8) * nbox;
         }
         double w = mixed ? 4 : 8;
-        st += 3 * w * nbox + w * nbox / 3;  // level-0 V-cycle vectors and restriction sums
+        // level-0 V-cycle vectors and restriction sums, as the step kernels take them (smoothers of
+        // degrees other than 2, lines that change along z): where strokes run, x alone is taken
+        st += 3 * w * nbox + w * nbox / 3;
         double m = nbox;
         for (int l = 1; l < 10 && m > 27; ++l) {
             m = (std::ceil(std::cbrt(m) / 3.0) + 2) * (std::ceil(std::cbrt(m) / 3.0) + 2) *

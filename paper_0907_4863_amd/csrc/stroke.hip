@@ -570,6 +570,7 @@ void l0_zinfo(FineLevel& L, hipStream_t s) {
         }
         lists.insert(lists.end(), tiles.begin(), tiles.end());
     }
+    L.n_tiles = (long)lists.size();
     const size_t bytes = sizeof(TileAt) * lists.size();
     L.tiles = (TileAt*)dmalloc(bytes, false);
     HIPCHECK(hipMemcpyAsync(L.tiles, lists.data(), bytes, hipMemcpyHostToDevice, s));

@@ -1,0 +1,42 @@
+"""The device bytes that a hierarchy reports are those it holds, to the byte, through re-setups,
+and saamg_footprint_bytes bounds a hierarchy and a solve state from
+above with every degree of the smoother (their level-0 vectors differ)."""
+import pytest
+
+import workloads as W
+
+torch = pytest.importorskip("torch")
+sa = pytest.importorskip("paper_0907_4863_amd")
+
+pytestmark = pytest.mark.gpu
+
+CASES = {"cylinder": (W.Shape.cylinder, (33, 33, 33), W.VARIANT_LIN, False),
+         "open ellipse": (lambda r, z: W.Shape.ellipse(r, 0.6, z), (61, 49, 161), W.VARIANT_QUAD, True),
+         "wide": (lambda r, z: W.Shape.ellipse(r, 0.6, z), (132, 60, 90), W.VARIANT_LIN, False)}
+
+
+@pytest.mark.parametrize("degree", [1, 2, 3])
+@pytest.mark.parametrize("precision", [sa.FP64, sa.MIXED])
+@pytest.mark.parametrize("name", CASES)
+def test_reported_and_bounded_bytes(name, precision, degree):
+    print(f"[case] device bytes, {name} precision={precision} degree={degree}", flush=True)
+    shape, dims, variant, open_ends = CASES[name]
+    dom, longer = (sa.domain_for(shape(1.0, z), *dims, open_ends=open_ends) for z in (4.0, 4.3))
+    al = sa.TorchAllocator()
+    G = sa.setup(dom, variant, sa.default_options(allocator=al, precision=precision, cheb_degree=degree))
+    hier, state = sa.footprint_bytes(dom.nx, dom.ny, dom.nz, variant, precision)
+
+    def check():
+        held = al.outstanding_bytes
+        assert sa.hierarchy_info(G)["device_bytes"] == held and held <= hier
+        return held
+
+    held = check()
+    b = torch.ones(dom.mask.size, dtype=torch.float64, device="cuda")
+    S = sa.state_create(G, b)
+    assert 0 < al.outstanding_bytes - held <= state
+    sa.state_destroy(S)
+    sa.refresh(G, longer)
+    check()
+    sa.destroy(G)
+    assert al.outstanding_bytes == 0
