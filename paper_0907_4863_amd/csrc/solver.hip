@@ -1514,6 +1514,7 @@ static void set_operator_impl(saamg_hierarchy* H, const saamg_domain* dom, hipSt
         op->sigma = nullptr;
         op->base = nullptr;
         op->zinfo = nullptr;
+        op->n_tab = 0;
         try {
             op->base = (int32_t*)dmalloc(4 * L.nseg, false);
             op->sigma = (double*)dmalloc(8 * L.nbox, false);

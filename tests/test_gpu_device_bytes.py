@@ -1,5 +1,5 @@
-"""The device bytes that a hierarchy reports are those it holds, to the byte, through re-setups,
-and saamg_footprint_bytes bounds a hierarchy and a solve state from
+"""The device bytes that a hierarchy reports are those it holds, to the byte, through re-setups and
+operators of its own, and saamg_footprint_bytes bounds a hierarchy and a solve state from
 above with every degree of the smoother (their level-0 vectors differ)."""
 import pytest
 
@@ -36,6 +36,9 @@ def test_reported_and_bounded_bytes(name, precision, degree):
     S = sa.state_create(G, b)
     assert 0 < al.outstanding_bytes - held <= state
     sa.state_destroy(S)
+    for _ in range(2):
+        sa.set_operator(G, longer)
+        assert check() > held
     sa.refresh(G, longer)
     check()
     sa.destroy(G)
