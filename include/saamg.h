@@ -309,7 +309,8 @@ int saamg_refresh(saamg_hierarchy* H, const saamg_domain* dom, void* stream);
  *           condition kind (as for saamg_refresh); copied.
  *   stream  work is queued on it; the call returns when the operator is complete.
  * Errors: SAAMG_INVALID_ARG when dom fails those checks or a solve state created on H
- * still exists (H unchanged); SAAMG_NOMEM, SAAMG_HIP_ERROR.
+ * still exists (H unchanged); SAAMG_NOMEM, SAAMG_HIP_ERROR (H unchanged, or without an
+ * operator set: later solves iterate with the one H was built or last refreshed for).
  */
 int saamg_set_operator(saamg_hierarchy* H, const saamg_domain* dom, void* stream);
 

@@ -1526,9 +1526,17 @@ static void set_operator_impl(saamg_hierarchy* H, const saamg_domain* dom, hipSt
         H->op = op;
         H->bytes += 8L * L.nbox + 4L * L.nseg + zinfo_bytes(L);
     }
-    H->bytes -= 12L * 16 * H->op->n_tab;
-    fine_numbers(*H->op, dom, dd, H->variant, s);
-    H->bytes += 12L * 16 * H->op->n_tab;
+    const long before = H->op->n_tab;
+    try {
+        fine_numbers(*H->op, dom, dd, H->variant, s);
+    } catch (...) {
+        // an operator without its rows or line information must not meet a solve
+        (void)hipStreamSynchronize(s);
+        H->op->n_tab = before;
+        drop_operator(H);
+        throw;
+    }
+    H->bytes += 12L * 16 * (H->op->n_tab - before);
 }
 
 template <class F>
