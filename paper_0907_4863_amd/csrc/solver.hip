@@ -564,8 +564,15 @@ static void state_alloc(saamg_state* S, saamg_hierarchy* H, bool pinned = true) 
 }
 
 static void state_release(saamg_state* S) {
-    // work that an error left behind may still write the pinned scalars and the vectors
-    if (S->busy) (void)hipDeviceSynchronize();
+    // work that an error left behind may still write the pinned scalars and the vectors: wait for
+    // the hierarchy's device, which need not be the current one
+    if (S->busy) {
+        int dev = 0;
+        const bool known = hipGetDevice(&dev) == hipSuccess;
+        (void)hipSetDevice(S->H->device);
+        (void)hipDeviceSynchronize();
+        if (known) (void)hipSetDevice(dev);
+    }
     S->busy = false;
     for (double* p : {S->x, S->r, S->q, S->bs}) dfree(p);
     dfree(S->p);
