@@ -17,7 +17,6 @@
 namespace saamg {
 
 constexpr int kColThreads = 256;
-constexpr int kColMaxPlanes = 60;
 
 // A lane's nodes in a plane, as byte offsets of values of 4 and 8 bytes: the 5 lines (own 1..3)
 // a pass loads, and the 3 it writes.
