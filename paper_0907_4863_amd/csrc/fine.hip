@@ -978,7 +978,7 @@ __global__ void __launch_bounds__(kThreads) k_l0_line_copy(long nlines, int nseg
     }
 }
 
-void l0_dedup_table(FineLevel& L, const double* full64, const float* full32, hipStream_t s) {
+void l0_dedup_table(FineLevel& L, const double* full64, const float* full32, bool counts, hipStream_t s) {
     const long nlines = (long)L.ny * L.nz;
     Tmp keep(4 * nlines, false), same(4 * nlines, false), off(4 * nlines, false), nb(4 * nlines, false),
         tot(8 * scan_words(nlines), false);
@@ -1007,8 +1007,7 @@ void l0_dedup_table(FineLevel& L, const double* full64, const float* full32, hip
                        (const int32_t*)keep.as<int32_t>(), (const int32_t*)off.as<int32_t>(),
                        L.n_irr, (long)n_tab, full64, full32, L.tab64, L.tab32);
     HIPCHECK(hipGetLastError());
-    l0_zinfo(L, s);
-    HIPCHECK(hipStreamSynchronize(s));
+    l0_zinfo(L, counts, s);
 }
 
 __global__ void __launch_bounds__(kThreads) k_unknown_list(L0View<double> v, const int32_t* ucnt_base,

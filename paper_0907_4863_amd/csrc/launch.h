@@ -128,8 +128,8 @@ void l0_build_table(FineLevel& L, const uint8_t* mask, const int32_t* nwidx, con
                     const double* nwfrac, int variant, double sigma0, double* rule, double* tab64,
                     float* tab32, hipStream_t s);
 // De-duplicated table of L from the full one: sets L.base, L.n_tab, L.tab64, L.tab32
-// (reallocated).  Synchronises the stream.
-void l0_dedup_table(FineLevel& L, const double* full64, const float* full32, hipStream_t s);
+// (reallocated), and the line information (counts: see l0_zinfo).  Synchronises the stream.
+void l0_dedup_table(FineLevel& L, const double* full64, const float* full32, bool counts, hipStream_t s);
 void l0_unknown_list(const FineLevel& L, long* out, hipStream_t s);  // requires n_unknowns slots
 
 // ---- level 0: operators
@@ -158,8 +158,8 @@ void l0_prolong(const FineLevel& L, const CoarseLevel& C, const T* v, T* x, doub
                 hipStream_t s);
 
 // ---- level 0, whole strokes of the V-cycle (stroke.hip)
-// L.zinfo from L's masks and table (allocated on first use)
-void l0_zinfo(FineLevel& L, hipStream_t s);
+// L.zinfo from L's masks and table (allocated on first use); with `counts` also how often lines change
+void l0_zinfo(FineLevel& L, bool counts, hipStream_t s);
 long zinfo_bytes(const FineLevel& L);
 // the share of planes where lines change, as the rules of the forms that keep rows take it
 double l0_change(const FineLevel& L);

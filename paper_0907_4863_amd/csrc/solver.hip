@@ -1146,9 +1146,10 @@ struct DeviceDomain {
 };
 
 // Level-0 numbers from the spacings, the Robin parameter and the near-wall fractions:
-// stencil weights of regular rows, the irregular rows' table and the scaling sigma.
+// stencil weights of regular rows, the irregular rows' table and the scaling sigma; with `counts`
+// also how often lines change along z, which the rules of the forms that keep rows read.
 static void fine_numbers(FineLevel& L, const saamg_domain* dom, const DeviceDomain& dd, int variant,
-                         hipStream_t s) {
+                         bool counts, hipStream_t s) {
     L.h[0] = dom->hx;
     L.h[1] = dom->hy;
     L.h[2] = dom->hz;
@@ -1161,7 +1162,7 @@ static void fine_numbers(FineLevel& L, const saamg_domain* dom, const DeviceDoma
     Tmp full64(8 * 16 * nr, false), full32(4 * 16 * nr, false), rule(32 * std::max<long>(dd.rows, 1), false);
     l0_build_table(L, dd.mask, dd.nwidx, dd.nwnodes, dd.rows, dd.nwfrac, variant, sigma0,
                    rule.as<double>(), full64.as<double>(), full32.as<float>(), s);
-    l0_dedup_table(L, full64.as<double>(), full32.as<float>(), s);
+    l0_dedup_table(L, full64.as<double>(), full32.as<float>(), counts, s);
 }
 
 // Smoother and transfer parameters of level l from its operator (Section 3.2).
@@ -1330,7 +1331,7 @@ static saamg_hierarchy* setup_impl(const saamg_domain* dom, int variant, const s
         }
         L.n_irr = tots[0];
         L.n_unknowns = tots[1];
-        fine_numbers(L, dom, dd, variant, s);
+        fine_numbers(L, dom, dd, variant, true, s);
         dd.release();
         H->bytes = 24L * L.nseg + 8L * nbox + 12L * 16 * L.n_tab + zinfo_bytes(L) +
                    (long)sizeof(TileAt) * L.n_tiles;
@@ -1481,7 +1482,7 @@ static void refresh_impl(saamg_hierarchy* H, const saamg_domain* dom, hipStream_
     H->bytes -= 12L * 16 * L.n_tab;
     const int bytes = H->opt.precision == SAAMG_MIXED ? 4 : 8;
     const bool by_strokes = strokes(H, bytes);
-    fine_numbers(L, dom, dd, H->variant, s);
+    fine_numbers(L, dom, dd, H->variant, true, s);
     H->bytes += 12L * 16 * L.n_tab;
     dd.release();
     if (H->ws && strokes(H, bytes) != by_strokes) {  // its vectors are those of the other form
@@ -1535,7 +1536,8 @@ static void set_operator_impl(saamg_hierarchy* H, const saamg_domain* dom, hipSt
     }
     const long before = H->op->n_tab;
     try {
-        fine_numbers(*H->op, dom, dd, H->variant, s);
+        // only the CG passes read it, where they may run by columns
+        fine_numbers(*H->op, dom, dd, H->variant, l0_cols_box(L), s);
     } catch (...) {
         // an operator without its rows or line information must not meet a solve
         (void)hipStreamSynchronize(s);

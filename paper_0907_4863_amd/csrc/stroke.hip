@@ -516,27 +516,32 @@ __global__ void __launch_bounds__(256) k_shadow(int nz, long words, const uint64
     if (m) atomicOr((unsigned long long*)&shadow[t], (unsigned long long)m);
 }
 
-void l0_zinfo(FineLevel& L, hipStream_t s) {
+void l0_zinfo(FineLevel& L, bool counts, hipStream_t s) {
     if (!L.zinfo) L.zinfo = (uint8_t*)dmalloc(zinfo_bytes(L), false);
-    const long lines = (long)L.ny * L.nz;
-    Tmp compat(lines, false);
-    hipLaunchKernelGGL(k_zcompat, dim3((unsigned)((lines + kBlockY - 1) / kBlockY)),
-                       dim3(kWave, kBlockY), 0, s, L.view<double>(), compat.as<uint8_t>());
-    hipLaunchKernelGGL(k_zinfo, dim3((unsigned)((zinfo_bytes(L) + 255) / 256)), dim3(256), 0, s,
-                       L.ny, L.nz, (const uint8_t*)compat.as<uint8_t>(), L.zinfo);
     // the unknowns never change, and with them neither do the tiles: the first time only
     const bool first = L.stroke[0][0].W == 0;
-    const long nrow = (L.ny + 2) / 3, words = first ? (long)L.ny * L.nsegx : 0;
-    Tmp sh(8 * (words + nrow), first);  // the shadow, then two counts an aggregate row
+    const long lines = (long)L.ny * L.nz, nrow = counts ? (L.ny + 2) / 3 : 0,
+               words = first ? (long)L.ny * L.nsegx : 0;
+    // the shadow, two counts an aggregate row, and a byte a line
+    Tmp sh(8 * (words + nrow) + lines, false);
+    uint8_t* compat = (uint8_t*)(sh.as<uint64_t>() + words + nrow);
+    hipLaunchKernelGGL(k_zcompat, dim3((unsigned)((lines + kBlockY - 1) / kBlockY)),
+                       dim3(kWave, kBlockY), 0, s, L.view<double>(), compat);
+    hipLaunchKernelGGL(k_zinfo, dim3((unsigned)((zinfo_bytes(L) + 255) / 256)), dim3(256), 0, s,
+                       L.ny, L.nz, (const uint8_t*)compat, L.zinfo);
     std::vector<uint64_t> got(words + nrow);
-    hipLaunchKernelGGL(k_zchange, dim3((unsigned)nrow), dim3(kWave), 0, s, L.ny, L.nz,
-                       (const uint8_t*)L.zinfo, (int*)(sh.as<uint64_t>() + words));
-    if (first)
+    if (counts)
+        hipLaunchKernelGGL(k_zchange, dim3((unsigned)nrow), dim3(kWave), 0, s, L.ny, L.nz,
+                           (const uint8_t*)L.zinfo, (int*)(sh.as<uint64_t>() + words));
+    if (first) {
+        zero_fill(sh.p, 8 * words, s);
         hipLaunchKernelGGL(k_shadow, dim3((unsigned)((words + 255) / 256), (unsigned)((L.nz + 31) / 32)),
                            dim3(256), 0, s, L.nz, words, (const uint64_t*)L.unk, sh.as<uint64_t>());
+    }
     HIPCHECK(hipGetLastError());
-    HIPCHECK(hipMemcpyAsync(got.data(), sh.p, 8 * got.size(), hipMemcpyDeviceToHost, s));
-    HIPCHECK(hipStreamSynchronize(s));  // also: the temporaries may go
+    if (!got.empty())
+        HIPCHECK(hipMemcpyAsync(got.data(), sh.p, 8 * got.size(), hipMemcpyDeviceToHost, s));
+    HIPCHECK(hipStreamSynchronize(s));  // also: the temporary may go
     long change = 0, planes = 0;
     L.change_worst = 0.0;
     for (long Y = 0; Y < nrow; ++Y) {
