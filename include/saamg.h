@@ -104,8 +104,9 @@ typedef struct {
                               multilevel hierarchies; the level's box with its ghost layer must
                               hold at most 8192 nodes)                         default DIRECT */
     int32_t coarse_sweeps; /* Gauss-Seidel sweeps (Section 3.2 uses 3)         default 3    */
-    /* Level-0 launch shape of the solve-time kernels of the CG iteration, and of the V-cycle's
-       when cheb_degree is not 2 (the fused degree-2 kernels choose their own) (results agree up to the order of
+    /* Level-0 launch shape of the solve-time kernels of the CG iteration and of the V-cycle
+       (the fused degree-2 V-cycle and the CG passes by columns, taken where the domain's
+       lines keep their stencil along z, choose their own; results agree up to the order of
        the dot products' partial sums): planes per block along z (0 = automatic; else a
        power of two 2..32, capped at 14 for fp32 and 30 for fp64 on 16-byte lanes) and
        64-node segments per block along x (0 = automatic; else 1, 2 or 4, at most the
@@ -171,7 +172,8 @@ typedef struct {
                                           /* below sharing rows)                           */
     int64_t table_rows_t[SAAMG_MAX_LEVELS]; /* and of A_l^T (nonsymmetric levels)           */
     /* host wall time of the setup's phases: domain checks made by the host (those of large
-       domains run on the device, in the next phase), level-0 operator (masks, table, scaling), spectral estimates, Galerkin products and their compression, the
+       domains run on the device, in the next phase), level-0 operator (masks, table,
+       scaling), spectral estimates, Galerkin products and their compression, the
        coarsest-level solver, fp32 copies */
     double t_setup_phase_ms[6];
     int32_t l0_wide;                      /* 1: level-0 kernels on 16-byte lanes          */
@@ -442,7 +444,8 @@ int saamg_pic_destroy(saamg_pic* P);
  * 3 prolongation from level 1, 4 CG direction update + product with A, 5 CG r update,
  * 6 all coarse-level kernels, 7 reduction finalisation, 8 x update from the ring of fp32
  * CG directions (mixed precision on 16-byte lanes; the other forms update x in class 4).
- * With the degree-2 smoother the level-0 V-cycle runs as two launches: one that does the
+ * With the degree-2 smoother, on domains whose lines keep their stencil along z (pipes, not
+ * tapers or spheres), the level-0 V-cycle runs as two launches: one that does the
  * pre-smoothing, the residual and the restriction counts in classes 0, 1 and 2 with a third
  * of its time and bytes each, and one that does the prolongation and both post-smoothing
  * steps in class 3 with a third and in class 0 with two thirds.

@@ -409,7 +409,9 @@ __global__ void __launch_bounds__(kColThreads) k_col_lz(StrokeView<double> v, co
 // plane is within a 32-bit byte offset.  The two passes against the fused q-recursion and its
 // r update (fine.hip), which stay below: 97 x 97 x 291 cavity (0.9 million unknowns) 59 -> 46
 // us, 128 x 128 x 256 ellipse 78 -> 57 us, mixed the same, 145 x 145 x 435 ellipse 218 -> 146 us;
-// 64 x 64 x 128 cylinder (0.4 million) 15 -> 20 us, 33^3 9 -> 14 us.  On the 16-byte lanes of
+// 64 x 64 x 128 cylinder (0.4 million) 15 -> 20 us, 33^3 9 -> 14 us.  Near the line whole solves
+// take, without over with columns, 0.99 (97^3 cylinder, 0.7 million), 1.03 (80 x 80 x 160, 0.8 million)
+// and 1.03 (112^3, 1.1 million), in both precisions.  On the 16-byte lanes of
 // wide.hip the passes were faster than by columns (256 x 256 x 768, fp32 direction: 138 + 227
 // us against 153 + 246).
 //

@@ -1158,7 +1158,9 @@ static CoefOut coef_out(const CoarseLevel& C) {
 // doubles; done: one byte per aggregate.
 //
 // From 32768 aggregates on: the column and the marks are two launches and two buffers more,
-// which at 64 x 64 x 128 (20,812 aggregates) cost what they save.
+// which on small domains cost what they save.  Galerkin phases with / without them: 9,537
+// aggregates (49 x 49 x 97) 0.34 / 0.33 ms, 20,812 (64 x 64 x 128) 0.37 / 0.38, 27,648 0.40 / 0.41,
+// 35,937 (97^3) 0.55 / 0.58, 70,785 0.66 / 0.78, 108,300 (112 x 112 x 224) 0.72 / 0.92.
 bool rap_marks(const CoarseLevel& C) { return (long)C.mx * C.my * C.mz >= 32768; }
 void rap_from_l0(const FineLevel& L, const CoarseLevel& C, double omega, double* con, uint8_t* done,
                  hipStream_t s) {

@@ -441,9 +441,10 @@ void l0_scatter_nwidx(int32_t* nwidx, const int64_t* nodes, long n, hipStream_t 
 // its 0.3 million wall entries into near-wall rows on the host, and uploaded 56 bytes a row
 // instead of the 17 of an entry.  Here the entries are checked where they lie and scattered
 // to sparse rows (an entry's row is that of the first entry of its node, an end-plane
-// unknown's behind all entries): the setup takes 6.6 ms.  Whatever these checks do not pass (entries that
-// are not sorted by node and direction, or any invalid domain) goes through prepare_domain,
-// which sorts them or names the error.
+// unknown's behind all entries): the setup took 6.6 ms then (5.1 with what followed).  Whatever
+// these checks do not pass (entries that are not sorted by node and direction, or any invalid
+// domain) goes through prepare_domain, which sorts them or names the error, and so does every
+// domain of a caller with an allocator of its own.
 
 // No unknown on a face of the box; with open ends, every end-plane unknown has one inside.
 __global__ void __launch_bounds__(256) k_check_faces(int nx, int ny, int nz, const uint8_t* __restrict__ mask,

@@ -1,5 +1,7 @@
-// Host-side preparation of a discrete domain for the setup (of small domains, and of those that
-// the checks on the device do not pass): argument checks and the near-wall rows (Section 2: the unknowns next to the wall and their wall fractions).
+// Host-side preparation of a discrete domain for the setup (of small domains, of those that the
+// checks on the device do not pass, and of a caller's with an allocator of its own): argument
+// checks and the near-wall rows (Section 2: the unknowns next to the wall and their wall
+// fractions).
 // Plain C++ with no HIP dependency, so that it can also be built and checked on its own.
 #pragma once
 

@@ -1051,8 +1051,9 @@ static void validate_options(const saamg_options& o) {
 
 // Whether the device checks the domain: its scalars are in range (prepare_domain names what is
 // not) and, where the mask is scanned, it has an unknown; and it has enough wall entries for
-// the uploads and launches to pay (3,720 at 33^3: 30 us on the host, 90 on the device; 31,248
-// at 64 x 64 x 128: 200 and 20).
+// the uploads and launches to pay.  Setups with the rows formed on the device / on the host: 3,720
+// entries (33^3) 1.33 / 1.29 ms, 10,672 (49 x 49 x 60) 1.52 / 1.49, 17,480 1.60 / 1.58, 24,304 (64 x 64
+// x 100) 1.73 / 1.73, 31,248 1.86 / 2.01, 72,192 (97 x 97 x 194) 2.49 / 2.76: they meet near 20,000.
 static bool device_checks(const saamg_domain* dom, int variant, bool scan_mask) {
     if (!dom || !dom->mask || dom->nx < 3 || dom->ny < 3 || dom->nz < 3) return false;
     const double nbox = (double)dom->nx * dom->ny * dom->nz;

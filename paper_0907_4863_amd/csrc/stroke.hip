@@ -20,11 +20,14 @@
 //
 // Why one pass: the seven step kernels moved 20 + 4 and 28 bytes a node in fp32 where the
 // strokes move 8 and 12, but each also paid a march's fixed cost per plane (masks, slots,
-// table rows, 5 to 9 loads a node), and on small boxes a launch of 4-5 us.  Vector
-// instructions bound the strokes (about 34 a node for the three stages of the down-stroke, 60%
-// of the issue slots busy on the largest boxes) and, on small boxes, the latency of a plane
-// step (0.45-0.6 us).  Time per V-cycle, step kernels -> down + up stroke:
-//   256 x 256 x 768 ellipse, quadratic rule, fp32   612 -> 122 + 176 us
+// table rows, 5 to 9 loads a node), and on small boxes a launch of 4-5 us.  On small boxes the
+// strokes are bound by the latency of a plane step (0.45-0.6 us).  On the largest no unit is
+// full: of 256 x 256 x 768 (fp32, down / up, counters) the vector units issue on 64 / 55% of the
+// cycles of a busy compute unit (67 and 83 instructions an unknown, halo included), compute units
+// are busy on 80% of the launch (480 blocks on 256 of them), 450 / 750 MB move at 3.6 / 4.1 TB/s
+// where a copy of the same run moves 4.8, and a wavefront waits for loads or its plane's barrier
+// on 54 / 59% of its cycles.  Time per V-cycle, step kernels -> down + up stroke:
+//   256 x 256 x 768 ellipse, quadratic rule, fp32   612 -> 122 + 177 us
 //   512^3 open tube, constant rule, fp32           1650 -> 308 + 455 us
 //   128 x 128 x 256 ellipse, quadratic rule, fp64   223 ->  28 +  33 us
 //   97 x 97 x 291 cavity with bore, fp32            118 ->  27 +  37 us
@@ -610,10 +613,10 @@ static std::vector<TileAt> live_tiles(const FineLevel& L, const std::vector<uint
 // with n wavefronts per SIMD and the blocks that hold unknowns.  a and b are the microseconds
 // of a plane step measured on boxes from 33^3 to 256 x 256 x 768 (fp32, 8 wavefronts a block:
 // 0.79 us with one block on a compute unit, 1.18 with two; fp64: 0.50 with one wavefront per
-// SIMD, 0.87 with two).  On a 128 x 128 x 256 box in fp64 (down / up): 27 planes (240 blocks)
-// 31.4 / 37.6 us, 24 planes (264 blocks, 8 of them in a second round) 51.9 / 61.9 us, 12 planes
-// 52.4 / 62.8 us; on the 256 x 256 x 768 ellipse in fp32 with 16 wavefronts 48 planes 169 / 204
-// us, 24 planes 177 / 215, 54 planes 193 / 236.
+// SIMD, 0.87 with two).  Single launches (down / up): 128 x 128 x 256 ellipse in fp64, 8 wavefronts,
+// 24 planes 30.5 / 35.7 us, 27 planes 32.6 / 38.5, 21 planes (a second round begun) 49.7 / 60.1, 12
+// planes 38.8 / 45.9; 256 x 256 x 768 ellipse in fp32, 16 wavefronts, 48 planes 145 / 179 us, 54 planes
+// 141 / 198, 24 planes 150 / 189, 57 planes 166 / 203.
 static StrokeTile stroke_tiling(const FineLevel& L, const std::vector<uint64_t>& shadow, bool up,
                                 int bytes, std::vector<TileAt>* tiles) {
     const int tx = up ? kUpX : kDownX;
