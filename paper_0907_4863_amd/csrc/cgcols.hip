@@ -428,7 +428,7 @@ bool l0_cols(const FineLevel& L) {
     if (L.nx > 128)
         most = L.nbox < 3000000 ? 1.0 : 0.7;
     else
-        most = L.nbox < 2000000 ? 0.05 : 0.3;
+        most = L.nbox < 2000000 ? 0.06 : 0.3;
     return l0_cols_box(L) && l0_change(L) <= most;
 }
 long l0_col_parts(const FineLevel& L) { return L.col.blocks(); }
